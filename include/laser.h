@@ -266,11 +266,12 @@ laser_status laser_model_create(const laser_model_desc* desc, laser_model** out)
 laser_status laser_model_set_tensor(laser_model* m, const char* name, const void* d_ptr, size_t bytes);
 
 /* Bytes of device workspace the model needs for forwards of up to max_rows rows
- * (tokens per forward: batch for decode, S*batch for a probe chunk; 1..64). */
+ * (tokens per forward: batch for decode, S*batch for a probe chunk; 1..64).  For bf16 models
+ * with d_ffn a multiple of 32 it includes room for prompts prefilled 512 tokens at a time. */
 laser_status laser_workspace_size(const laser_model* m, int max_rows, size_t* bytes);
 
 /* Checks that every tensor is set, lays out the caller's workspace (>= the size above
- * for max_rows) and fills its constant tables (RoPE cos/sin computed on the host in
+ * for max_rows; without the room for wide prefills, prompts run max_rows tokens at a time) and fills its constant tables (RoPE cos/sin computed on the host in
  * double precision) with asynchronous copies on `stream`.  The workspace must stay
  * allocated until laser_model_destroy. */
 laser_status laser_model_finalize(laser_model* m, int max_rows, void* d_workspace, size_t bytes, void* stream);
@@ -331,7 +332,7 @@ laser_status laser_kv_destroy(laser_kv* kv);
 /* ========================================================================== */
 
 /* Runs n prompt tokens d_tokens[0..n-1] of seq_id at its current length (chunks of at
- * most max_rows rows), appending their K/V.  d_logits_last (vocab floats or NULL)
+ * most 512 rows where the workspace has room for them, else max_rows), appending their K/V.  d_logits_last (vocab floats or NULL)
  * receives the last token's logits. */
 laser_status laser_prefill(laser_model* m, laser_kv* kv, int seq_id, const int32_t* d_tokens, int n,
                            float* d_logits_last, void* stream);
@@ -469,20 +470,22 @@ laser_status laser_model_set_graphs(laser_model* m, int enable);
  * Host-side only.  Errors: LASER_ERR_STATE (bad model), LASER_ERR_INVALID_ARG (null). */
 laser_status laser_model_graph_stats(const laser_model* m, long long* captures, int* cached);
 
-/* Projection kernel choice on the matrix-core path (forwards of 3 to 64 rows; the linear
+/* Projection kernel choice on the matrix-core path (forwards of 3 rows and more; the linear
  * maps of the transformer block in the decode steps and the trial-answer probe of
- * Section 3.1, whose costs Eq. 2 sums).  Two kernels compute the same products: one
- * splits K over the waves of a workgroup (1-4 row groups of 16 weight rows per
- * workgroup), the other gives each of 4 waves its own row groups and stages the
- * activations once per workgroup in LDS.  mode 0 (the default) takes the second for the
- * gate/up projection of forwards of 33 to 64 rows when it has enough row groups and for
- * the O and down projections of forwards of 49 to 64 rows, and the first elsewhere; it
- * also computes the QKV projection of bf16 models in forwards of 33 to 64 rows over
- * 512-column slices of K (each slice's activations staged once in LDS for 16 row groups,
- * the slices summed by a second kernel).  1 uses only the first kernel; 2 the second
- * wherever it applies (K a multiple of 8).  The summation order differs between them, so
- * results may differ in the last bits.  Captured forwards are released when the mode
- * changes.  Errors: LASER_ERR_STATE (bad model), LASER_ERR_INVALID_ARG (mode). */
+ * Section 3.1, whose costs Eq. 2 sums).  Three kernels compute the same products: one splits K
+ * over the waves of a workgroup (1-4 row groups of 16 weight rows per workgroup); one gives
+ * each of 4 waves its own row groups and stages the activations once per workgroup in LDS; one
+ * reads activations that the producing kernel stored as matrix-core fragments.  mode 0 (the
+ * default) takes the third for forwards of 17 rows and more of bf16 models with d_ffn a
+ * multiple of 32, and prefills prompts up to 512 rows per forward with it; elsewhere the second
+ * for the gate/up projection of forwards of 33 to 64 rows when it has enough row groups and for
+ * the O and down projections of forwards of 49 to 64 rows, and the first otherwise (QKV of bf16
+ * models at 33 to 64 rows: over 512-column slices of K, each slice's activations staged once
+ * in LDS for 16 row groups, the slices summed by a second kernel).  1 uses only the first
+ * kernel; 2 the second wherever it applies (K a multiple of 8); both prefill in chunks of
+ * max_rows rows.  The summation order differs between them, so results may differ in the last
+ * bits.  Captured forwards are released when the mode changes.  Errors: LASER_ERR_STATE (bad
+ * model), LASER_ERR_INVALID_ARG (mode). */
 laser_status laser_model_set_gemm_kernel(laser_model* m, int mode);
 
 /* Attention split merge.  The decode step's paged attention (Section 3.1's chain-of-thought

@@ -25,13 +25,19 @@ PROBES = os.path.join(LIBDIR, "design_probes")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
-HIP_SOURCES = ["gemm.hip", "attn.hip", "misc.hip", "runtime.cpp", "pages.cpp"]
+HIP_SOURCES = ["gemm.hip", "gemm_frag.hip", "attn.hip", "misc.hip", "runtime.cpp", "pages.cpp"]
 C_SOURCES = ["controller.c", "sim.c"]
 HIP_FLAGS = [
     f"--offload-arch={ARCH}", "-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-result",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     f"-I{INCLUDE}", f"-I{CSRC}",
 ]
+# Matrix-core accumulators in ordinary vector registers: in the ring loop of gemm_frag.hip the
+# compiler otherwise moves every accumulator between the two register files each step (120 moves
+# beside 40 matrix-core instructions).  Other files' kernels measured no gain or a loss (3-tile
+# K-split kernel: a 37-row prefill 0.986 -> 1.032 ms).
+MFMA_VGPR = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
+EXTRA_FLAGS = {"gemm_frag.hip": MFMA_VGPR}
 C_FLAGS = ["-O2", "-fPIC", "-std=c99", "-Wall", "-ffp-contract=off", f"-I{INCLUDE}", f"-I{CSRC}"]
 
 
@@ -47,7 +53,7 @@ def _compile(src):
     if src.endswith(".c"):
         cmd = ["gcc", *C_FLAGS, "-c", path, "-o", obj]
     else:
-        cmd = [HIPCC, *HIP_FLAGS, "-x", "hip", "-c", path, "-o", obj]
+        cmd = [HIPCC, *HIP_FLAGS, *EXTRA_FLAGS.get(src, []), "-x", "hip", "-c", path, "-o", obj]
     rc, out = _run(cmd)
     return src, obj, rc, out, cmd
 

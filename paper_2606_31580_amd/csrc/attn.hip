@@ -91,7 +91,7 @@ __global__ __launch_bounds__(64 * kAttnWaves) void k_attn(AttnArgs a) {
     qv[i] = *(const float4*)(a.q + ((size_t)row * a.hq + head) * HD + d);
   }
   static_assert(NC <= 64 * kAttnWaves, "one position per thread");
-  const int cpos_loaded = a.plan->rows[wi.row0 + min(col0 + tid, NQ - 1) / a.G].pos;  // column tid's position
+  const int cpos_loaded = row_desc(a.plan, wi.row0 + min(col0 + tid, NQ - 1) / a.G).pos;  // column tid's position
 
   // Page operands are loaded D pages ahead of their use into a ring of raw buffers (bf16
   // bits; fp32 pools are split into bf16 hi/lo when used).  A decode split is usually two
@@ -362,12 +362,17 @@ __global__ __launch_bounds__(64 * kAttnWaves) void k_attn(AttnArgs a) {
     // ---- the tile's columns: the output (one workgroup) or the workgroup's partial
     if (c < NQ) {
       const int row = wi.row0 + c / a.G, head = kvh * a.G + c % a.G;
-      const size_t col = ((size_t)kvh * kAttnMaxWG + ((wi.info >> 8) & 0xffff)) * ncols + (size_t)wi.row0 * a.G + c;
+      const size_t col = ((size_t)kvh * a.max_wg + ((wi.info >> 8) & 0xffff)) * ncols + (size_t)wi.row0 * a.G + c;
       if (wi.info & (1 << 24)) {
-        float* out = a.o + ((size_t)row * a.hq + head) * HD;
         const float inv = 1.f / l_run;
+        if (a.ofrag != nullptr) {
 #pragma unroll
-        for (int dt = 0; dt < ND; ++dt) *(f32x4*)(out + 16 * dt + 4 * lg) = o[dt] * inv;
+          for (int dt = 0; dt < ND; ++dt) st_frag4(a.ofrag, row, head * HD + 16 * dt + 4 * lg, a.hq * HD >> 5, o[dt] * inv);
+        } else {
+          float* out = a.o + ((size_t)row * a.hq + head) * HD;
+#pragma unroll
+          for (int dt = 0; dt < ND; ++dt) *(f32x4*)(out + 16 * dt + 4 * lg) = o[dt] * inv;
+        }
       } else if (fuse_n) {  // device-scope stores: another XCD's workgroup may merge them
 #pragma unroll
         for (int dt = 0; dt < ND; ++dt) st_dev16(rpart, (uint32_t)((col * HD + 16 * dt + 4 * lg) * 4), o[dt]);
@@ -407,7 +412,7 @@ __global__ __launch_bounds__(64 * kAttnWaves) void k_attn(AttnArgs a) {
       i32x2 mv[B];
 #pragma unroll
       for (int j = 0; j < B; ++j) {  // past the count: slot fuse_n - 1 again (ignored below)
-        const size_t colx = ((size_t)kvh * kAttnMaxWG + min(s0 + j, fuse_n - 1)) * ncols + colb;
+        const size_t colx = ((size_t)kvh * a.max_wg + min(s0 + j, fuse_n - 1)) * ncols + colb;
         ov[j] = ld_dev16(rpart, (uint32_t)((colx * HD + 4 * d4) * 4));
         mv[j] = ld_dev8(rml, (uint32_t)(colx * 8));
       }
@@ -438,7 +443,8 @@ __global__ __launch_bounds__(64 * kAttnWaves) void k_attn(AttnArgs a) {
 // loads issued together before the plan lookup.  Each wave combines its slots across its
 // lanes, then the waves are combined in LDS in fixed order.
 constexpr int kMergeWaves = 8;
-template <int HD>
+// FRAG: the output goes out as fragments (a.ofrag).
+template <int HD, bool FRAG>
 __global__ __launch_bounds__(64 * kMergeWaves) void k_attn_merge(AttnArgs a, int nslots) {
   constexpr int LPS = HD / 4;             // lanes per slot
   constexpr int SPW = 64 / LPS;           // slots per wave load
@@ -453,6 +459,7 @@ __global__ __launch_bounds__(64 * kMergeWaves) void k_attn_merge(AttnArgs a, int
   const int kvh = head / a.G, gi = head - kvh * a.G;
   const size_t ncols = (size_t)a.max_rows * a.G;
   const size_t col = (size_t)row * a.G + gi;
+  const int max_wg = FRAG ? a.max_wg : kAttnMaxWG;  // (only wide prefills have another layout)
   // Slots at or past nslots (the launch's bound on every group's count) read slot
   // nslots - 1 again, a cached line, instead of stale partials; slots past the row's own
   // count are replaced below, never combined.  The loads stay unconditional so none waits
@@ -462,13 +469,13 @@ __global__ __launch_bounds__(64 * kMergeWaves) void k_attn_merge(AttnArgs a, int
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
     const int slot = min(SPP * i + SPW * v + sl, nslots - 1);
-    const size_t sb = ((size_t)kvh * kAttnMaxWG + slot) * ncols + col;
+    const size_t sb = ((size_t)kvh * max_wg + slot) * ncols + col;
     const float2 ml = *(const float2*)(a.ml + sb * 2);
     mv[i] = ml.x;
     lv[i] = ml.y;
     ov[i] = *(const f32x4*)(a.part + sb * HD + 4 * d4);
   }
-  const int nwg = a.plan->row_nslots[row];
+  const int nwg = !FRAG || row < kMaxRows ? a.plan->row_nslots[row] : a.plan->wide_nslots[row / kMaxRows];
   if (nwg <= 1) return;  // written directly by the attention kernel
 #pragma unroll
   for (int i = 0; i < PER; ++i)
@@ -516,14 +523,32 @@ __global__ __launch_bounds__(64 * kMergeWaves) void k_attn_merge(AttnArgs a, int
       Lt += s_l[u] * f;
       Ot += s_o[u][d] * f;
     }
-    a.o[((size_t)row * a.hq + head) * HD + d] = Ot / Lt;
+    const float ov2 = Ot / Lt;
+    if constexpr (!FRAG) {
+      a.o[((size_t)row * a.hq + head) * HD + d] = ov2;
+    } else {  // as fragments: even lanes store two columns' hi parts, odd lanes their lo parts
+      uint16_t hi, lo;
+      split_bf16(ov2, hi, lo);
+      const uint32_t mine = (uint32_t)hi | ((uint32_t)lo << 16);
+      const uint32_t other = __float_as_uint(dpp_f<kDppQuad1032>(__uint_as_float(mine)));
+      const bool odd = d & 1;
+      const uint32_t w2 = odd ? (other >> 16) | (mine & 0xffff0000u) : (mine & 0xffffu) | (other << 16);
+      const int col = head * HD + (d & ~1);
+      const size_t off = frag_off(row, col & ~7, a.hq * HD >> 5) + 2 * (col & 7);
+      *(uint32_t*)(a.ofrag + (odd ? off ^ 64 : off)) = w2;
+    }
   }
 }
 
 hipError_t launch_attn_merge(const AttnArgs& a, int M, int hd, int nslots, hipStream_t s) {
-  if (nslots < 1 || nslots > kAttnMaxWG) return hipErrorInvalidValue;
-  if (hd == 128) return launch_k(k_attn_merge<128>, dim3(M, a.hq), dim3(64 * kMergeWaves), s, a, nslots);
-  if (hd == 64) return launch_k(k_attn_merge<64>, dim3(M, a.hq), dim3(64 * kMergeWaves), s, a, nslots);
+  if (nslots < 1 || nslots > a.max_wg) return hipErrorInvalidValue;
+  const dim3 grid(M, a.hq), block(64 * kMergeWaves);
+  if (hd == 128)
+    return a.ofrag ? launch_k(k_attn_merge<128, true>, grid, block, s, a, nslots)
+                   : launch_k(k_attn_merge<128, false>, grid, block, s, a, nslots);
+  if (hd == 64)
+    return a.ofrag ? launch_k(k_attn_merge<64, true>, grid, block, s, a, nslots)
+                   : launch_k(k_attn_merge<64, false>, grid, block, s, a, nslots);
   return hipErrorInvalidValue;
 }
 

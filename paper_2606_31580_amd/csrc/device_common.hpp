@@ -83,6 +83,41 @@ __device__ __forceinline__ void split_trunc2(float x0, float x1, uint32_t& hi, u
   lo = __builtin_amdgcn_perm(r1, r0, 0x07060302u);
 }
 
+// Fragment order of an activation matrix with `steps` 32-column steps per row: block (16-row
+// tile, step) is 16 rows x 128 bytes, a row's line holding its 32 columns' hi and lo parts in 8
+// chunks of 16 bytes (8 columns).  A row-wise producer writes whole lines, and chunk c of row r
+// sits at place c ^ (r / 2), so that the 16 rows a matrix-core operand reads at once fall in 16
+// different LDS bank groups.  Byte offset of the hi chunk of columns col .. col + 7 (col a
+// multiple of 8); the lo chunk is at that offset ^ 64.
+__device__ __forceinline__ size_t frag_off(int row, int col, int steps) {
+  return ((size_t)(row >> 4) * steps + (col >> 5)) * 2048 + (row & 15) * 128 + ((((col & 31) >> 3) ^ ((row & 15) >> 1)) * 16);
+}
+// Stores 4 consecutive columns (col a multiple of 4) of a row as fragments: 8 bytes of hi, 8 of lo.
+__device__ __forceinline__ void st_frag4(char* frag, int row, int col, int steps, f32x4 v) {
+  s16x4 hi, lo;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    uint16_t h, l;
+    split_bf16(v[q], h, l);
+    hi[q] = (short)h;
+    lo[q] = (short)l;
+  }
+  const size_t d = frag_off(row, col & ~7, steps) + 2 * (col & 7);
+  *(s16x4*)(frag + d) = hi;
+  *(s16x4*)(frag + (d ^ 64)) = lo;
+}
+// Eight values as packed bf16 hi and lo parts (rounded, split_bf16).
+__device__ __forceinline__ void split8(const float* v, u32x4& hi, u32x4& lo) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    uint16_t h0, l0, h1, l1;
+    split_bf16(v[2 * q], h0, l0);
+    split_bf16(v[2 * q + 1], h1, l1);
+    hi[q] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+    lo[q] = (uint32_t)l0 | ((uint32_t)l1 << 16);
+  }
+}
+
 // Loads through the global address space.  A pointer built by arithmetic, or picked among
 // several tensors, is otherwise read with flat instructions, which count against the LDS and
 // scalar-load counter as well: every later wait on that counter then covers them too.
@@ -94,6 +129,23 @@ __device__ __forceinline__ T ld_global(const void* p) {
 }
 __device__ __forceinline__ u32x4 ld_nt16(const void* p) { return __builtin_nontemporal_load((global_ptr<u32x4>)p); }
 __device__ __forceinline__ u32x2 ld_nt8(const void* p) { return __builtin_nontemporal_load((global_ptr<u32x2>)p); }
+
+// Copies 16 bytes per lane from global memory to LDS (lane i: lds + 16 i), asynchronously; the
+// wave's vector-memory counter tells when it is there (NT: non-temporal, for what is read once).  Inline asm rather than the builtin: for
+// the builtin the compiler makes every later LDS read wait for all copies in flight.
+template <bool NT>
+__device__ __forceinline__ void copy_to_lds16(const char* g, unsigned lds) {
+  if (NT)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(lds), "v"(g) : "memory");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(g) : "memory");
+}
+// Workgroup barrier that waits for no copies in flight.
+__device__ __forceinline__ void wg_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
 
 // Cross-lane primitives of gfx950 (no LDS traffic): DPP inside 16-lane rows, and the
 // permlane swaps across rows.  permlane16_swap(a, b) leaves (a.r0, b.r0, a.r2, b.r2) and

@@ -9,6 +9,7 @@
 namespace laser {
 
 constexpr int kMaxRows = 64;      // rows (tokens) of one forward
+constexpr int kFragRows = 512;    // rows of one prompt-prefill forward on the fragment path
 constexpr int kPage = 16;         // positions per KV page
 constexpr int kMaxBt = 1024;      // block-table updates carried by one plan
 constexpr int kAttnWaves = 4;     // waves per attention workgroup (one split each)
@@ -73,13 +74,24 @@ struct alignas(16) Plan {  // (16-byte aligned arrays: k_plan_fetch copies 16-by
   // reaches once this forward's merge workgroups of that layer have stored their outputs
   unsigned merge_target;
   PlanIO io;
-  RowDesc rows[kMaxRows];
+  RowDesc rows[kMaxRows];  // row m of a wider prefill forward: row_desc
   int row_nslots[kMaxRows];  // attention partial slots of each row (over all its groups)
+  int wide_nslots[kFragRows / kMaxRows];  // of the rows kMaxRows g and up of a wider prefill forward
   OutDesc outs[kMaxRows];
   alignas(16) AttnItem items[kMaxAttnItems];
   alignas(16) BtUpdate bt[kMaxBt];
   GroupDesc groups[kMaxGroups];  // (host side: the kernels read the work items)
 };
+
+// Row m of a forward.  A prefill forward of more than kMaxRows rows holds one sequence, so its
+// later rows follow from the first kMaxRows: the same sequence, as many positions on.
+__host__ __device__ inline RowDesc row_desc(const Plan* p, int m) {
+  RowDesc r = p->rows[m & (kMaxRows - 1)];
+  const int up = m & ~(kMaxRows - 1);
+  r.pos += up;
+  r.tok_off += up;
+  return r;
+}
 
 // Softmax statistics of one group of vocabulary rows for one output row.
 struct LmPart {
@@ -139,6 +151,12 @@ struct GemmArgs {
   // EPI_SWIGLU
   float* act;  // [M][F]
   int F;
+  // Fragment path (launch_gemm_frag): the activations as fragments, the SwiGLU output's
+  // fragments, row blocks of the grid (set by the launch)
+  const char* afrag;
+  char* frag_out;
+  const float* row_scale;  // the rows' 1 / rms (EPI_QKV, EPI_SWIGLU)
+  int fr_mblocks;
   // EPI_LMHEAD (logits destinations come from plan->io)
   LmPart* lm_part;  // [M][n_groups]
 };
@@ -153,8 +171,10 @@ struct AttnArgs {
   int max_pps, num_pages, layer;
   int hq, hkv, G, max_rows;
   float scale_log2;
-  float* part;  // [hkv][kAttnMaxWG][max_rows*G][hd]
-  float* ml;    // [hkv][kAttnMaxWG][max_rows*G][2]
+  float* part;  // [hkv][max_wg][max_rows*G][hd]
+  float* ml;    // [hkv][max_wg][max_rows*G][2]
+  int max_wg;   // partial slots per (kv head, column): kAttnMaxWG, fewer when a wide prefill's rows share the buffer
+  char* ofrag;  // the output as fragments for the O-projection (null: fp32 rows in o)
   uint32_t part_bytes, ml_bytes;
   unsigned* cnt;  // fused groups' arrival counters [hkv][kMaxGroups] x kAttnCntStride; zero between kernels
 };
@@ -211,6 +231,31 @@ hipError_t launch_gemv_merged(int dtype, int rw, const GemmArgs& a, const MergeA
 // then the summing / norm / epilogue kernel.
 constexpr int kQSliceSteps = 16, kQSliceGroups = 16;
 hipError_t launch_qkv_slices(const GemmArgs& a, float* qpart, float* sqpart, hipStream_t s);
+// Fragment path (bf16 weights, K a multiple of 32): activations and SwiGLU outputs as matrix-core
+// fragments (frag_off).  Residual projections and QKV write a.ksplit (1, 2, 4, 8) K shares to
+// kpart [share][M][N], ksplit x M <= kFragPartRows; launch_resid_norm adds them to h,
+// launch_qkv_epi makes q, K and V of them.
+// Workgroup shapes: WM x WN waves of MTW tiles (16 rows) by NGW groups (16 weight rows), a ring of
+// NS steps.  Up to 64 rows: one tile row, each wave a group of its own, so that a CU streams its
+// weights with 8 waves' copies (8 x 1 groups against 4 x 2, 8B gate/up at 40 rows: 43.8 against
+// 50.0 us).  More rows: tiles by groups as square as 160 KB of LDS allow.
+#define LASER_FRAG_SHAPES                                                                                     \
+  LASER_FRAG(2, 1, 1, 4, 6) LASER_FRAG(2, 1, 1, 5, 6) LASER_FRAG(2, 1, 1, 7, 6) LASER_FRAG(2, 1, 1, 8, 6)     \
+  LASER_FRAG(2, 1, 1, 10, 6) LASER_FRAG(3, 1, 1, 4, 6) LASER_FRAG(3, 1, 1, 5, 6) LASER_FRAG(3, 1, 1, 7, 6)    \
+  LASER_FRAG(3, 1, 1, 8, 6) LASER_FRAG(3, 1, 1, 10, 6) LASER_FRAG(4, 1, 1, 4, 6) LASER_FRAG(4, 1, 1, 5, 6)    \
+  LASER_FRAG(4, 1, 1, 7, 6) LASER_FRAG(4, 1, 1, 8, 6) LASER_FRAG(4, 1, 1, 10, 6) LASER_FRAG(4, 2, 2, 2, 3)    \
+  LASER_FRAG(3, 4, 2, 2, 3) LASER_FRAG(4, 3, 2, 2, 3) LASER_FRAG(4, 4, 2, 2, 3) LASER_FRAG(4, 5, 2, 2, 3)     \
+  LASER_FRAG(4, 4, 4, 2, 3) LASER_FRAG(4, 5, 4, 2, 3)
+constexpr int frag_cfg(int mtw, int ngw, int wm, int wn) { return mtw * 1000 + ngw * 100 + wm * 20 + wn; }
+constexpr int kFragPartRows = 2048;
+hipError_t launch_gemm_frag(int epi, int cfg, const GemmArgs& a, hipStream_t s);
+// The QKV epilogue on K shares (qpart [nslices][M][N]): their sum, times the row's 1 / rms
+// (a.row_scale, or from the slices' sums of squares sqpart), bias, rotation, q, K/V append.
+hipError_t launch_qkv_epi(const GemmArgs& a, const float* qpart, const float* sqpart, int nslices, hipStream_t s);
+// h[m] += kpart[0][m] + kpart[1][m] + ... (ksplit 0: h as it is); with a gain, also the row's
+// gain times h as fragments in xfrag and its 1 / rms in row_scale.
+hipError_t launch_resid_norm(float* h, const float* kpart, int ksplit, int M, int N, const void* gain, float eps,
+                             char* xfrag, float* row_scale, hipStream_t s);
 // Writes the tile-order copy of one projection's weights (the MFMA path's 16-row groups of
 // `a`, as weight_row maps them) to dst: a.n_groups groups x ceil(K/32) steps.
 hipError_t launch_tile_weights(int dtype, int epi, const GemmArgs& a, char* dst, hipStream_t s);

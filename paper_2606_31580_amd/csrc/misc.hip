@@ -22,7 +22,7 @@ __global__ __launch_bounds__(64) void k_embed(const Plan* plan, const void* embe
                                               int max_pps) {
   if (blockIdx.x == 0 && blockIdx.y == 0) apply_bt_updates(plan, bt, max_pps);
   const int m = blockIdx.x, g = blockIdx.y, j = threadIdx.x;
-  const RowDesc rd = plan->rows[m];
+  const RowDesc rd = row_desc(plan, m);
   int tok = plan->io.tok_src[rd.tok_sel][rd.tok_off];
   if (tok < 0 || tok >= vocab) tok = 0;  // ids outside the vocabulary never index past the table
   h[(size_t)m * d + 64 * g + j] = ldw<WT>(embed, (size_t)tok * d + 64 * g + j);

@@ -81,6 +81,7 @@ constexpr int kTargetAttnWaves = LASER_ATTN_TARGET_WAVES;  // attention waves a 
 #define LASER_ATTN_MAX_PPS 4
 #endif
 constexpr int kMaxPagesPerWave = LASER_ATTN_MAX_PPS;
+constexpr int kWidePagesPerWave = 16;  // the same for prefill forwards of more than kMaxRows rows
 // Splits of a one-row group that merges inside the attention kernel: its last workgroup reads
 // every split's partial (G columns x (hd + 2) floats each), so fewer, longer splits shorten
 // that tail; the bound trades it against how many workgroups stream the group's pages.
@@ -95,6 +96,8 @@ constexpr int kFusedMaxSplits = LASER_ATTN_FUSED_SPLITS;
 constexpr size_t kMergeMinOBytes = (size_t)16 << 20;
 
 struct Layout {
+  size_t xfrag, row_scale;  // the fragment path's gain times h, the rows' 1 / rms
+  int frag_rows;  // rows the fragment path's buffers hold (0: it is not used)
   size_t rope, h, q, o, act, kpart, kcnt, mcnt, qpart, sqpart, lm_part, attn_part, attn_ml, attn_cnt, plans, probe_p, tok_buf,
       p_buf, total;
   size_t attn_part_bytes, attn_ml_bytes, attn_cnt_bytes, kcnt_bytes, mcnt_bytes;
@@ -106,6 +109,7 @@ struct Layout {
 struct FwdKey {
   int M, n_out, agx, mslots, merge;  // agx: attention work items (grid width)
   int mo;                              // the split merge runs in the O-projection's launch
+  int frag;                            // the projections run on the fragment path (fixed by M)
   uint64_t kv_id;
   // same launches apart from the attention grid width
   bool same_shape(const FwdKey& o) const {
@@ -393,6 +397,43 @@ static MfmaShape mfma_shape(int epi, int n_groups, int M, int K, int es, int cus
   return best;
 }
 
+// Fragment path: workgroup shape and K shares of a projection.  What a workgroup copies (2 tiles
+// + groups KB per 32-column step) is what its time follows: 20-27 ns per KB measured at every
+// shape from 48 rows x 4 groups to 256 rows x 10, so the choice minimises, over the workgroups of
+// the busiest CU, steps x KB plus a start-up, plus the K shares' partial sums written and read
+// back.  Measured at 7B: gate/up of 40 rows 49.8 us with 10 groups (237 workgroups), 73.5 with 8
+// (296, two on 40 CUs); of 256 rows 125 us with 256 x 10, 161 with 128 x 8.
+struct FragShape {
+  int cfg, ks;
+};
+static FragShape frag_shape(int epi, int n_groups, int M, int K, int cus) {
+  struct C {
+    int mtw, ngw, wm, wn;
+  };
+#define LASER_FRAG(MTW, NGW, WM, WN, NS) {MTW, NGW, WM, WN},
+  static const C kCfg[] = {LASER_FRAG_SHAPES};
+#undef LASER_FRAG
+  const int tiles = ceil_div(M, 16), steps = K / 32;
+  FragShape best{frag_cfg(4, 1, 1, 8), 1};
+  double best_cost = 1e300;
+  for (const C& c : kCfg) {
+    const int mt = c.mtw * c.wm, ng = c.ngw * c.wn;
+    const int mblocks = ceil_div(tiles, mt), nblocks = ceil_div(n_groups, ng);
+    const double step = 0.024 * (2 * mt + ng);  // us
+    for (int ks = 1; ks <= (epi == EPI_SWIGLU ? 1 : 8); ks *= 2) {
+      if (ks * M > kFragPartRows || ks > steps) break;
+      const double rounds = ceil_div(mblocks * nblocks * ks, cus);
+      const double part = epi == EPI_SWIGLU ? 0.0 : 2e-6 * 16.0 * ks * M * n_groups;  // 8 bytes at 4 TB/s
+      const double cost = rounds * (step * steps / ks + 2.5) + part;
+      if (cost < best_cost) {
+        best_cost = cost;
+        best = {frag_cfg(c.mtw, c.ngw, c.wm, c.wn), ks};
+      }
+    }
+  }
+  return best;
+}
+
 // QKV over K slices (launch_qkv_slices): forwards of kQSliceMinRows to 64 rows, bf16 weights
 // (tile order when the copy is there).  Each workgroup stages a 512-column slice of K of every
 // activation row in LDS and runs 16 row groups over it.  Measured against the K-split kernel,
@@ -411,8 +452,20 @@ static size_t ks_cnt_bytes(const laser_model_desc& d) {
   return (size_t)ceil_div(d.d_model, 16) * kKsCntStride * 4;
 }
 
-static Layout make_layout(const laser_model_desc& d, int max_rows) {
+// The fragment path (launch_gemm_frag): bf16 weights, K of every projection a multiple of 32.
+// Forwards of kFragMinRows rows and more take it; a prompt's prefill takes up to kFragRows rows
+// per forward, so that 256 rows read the weights once and not 4 or 16 times.  Below 17 rows (one
+// 16-row tile) the activations are a small part of what a workgroup reads and the K-split kernel
+// is at least as fast.
+constexpr int kFragMinRows = 17;
+static bool frag_fit(const laser_model_desc& d) {
+  return d.dtype == LASER_DTYPE_BF16 && d.d_ffn % 32 == 0 && d.d_model <= 16384;
+}
+
+// wide: with the fragment path's buffers (finalize also takes a workspace without them).
+static Layout make_layout(const laser_model_desc& d, int max_rows, bool wide = true) {
   Layout L{};
+  L.frag_rows = wide && frag_fit(d) ? kFragRows : 0;
   const int hd = d.head_dim, G = d.n_q_heads / d.n_kv_heads;
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -421,11 +474,19 @@ static Layout make_layout(const laser_model_desc& d, int max_rows) {
     return o;
   };
   L.rope = take((size_t)d.max_positions * (hd / 2) * sizeof(float2));
-  L.h = take((size_t)max_rows * d.d_model * 4);
-  L.q = take((size_t)max_rows * d.n_q_heads * hd * 4);
-  L.o = take((size_t)max_rows * d.n_q_heads * hd * 4);
-  L.act = take((size_t)max_rows * d.d_ffn * 4);
-  L.kpart = take((size_t)kMaxKsplit * max_rows * d.d_model * 4);  // K-share partials of O-proj / down
+  const size_t rows = std::max(max_rows, L.frag_rows);  // (o and act: fp32 rows or fragments, 4 bytes per value)
+  L.h = take(rows * d.d_model * 4);
+  L.q = take(rows * d.n_q_heads * hd * 4);
+  L.o = take(rows * d.n_q_heads * hd * 4);
+  L.act = take(rows * d.d_ffn * 4);
+  if (L.frag_rows) {
+    L.xfrag = take(rows * d.d_model * 4);
+    L.row_scale = take(rows * 4);
+  }
+  // K-share partials of O-proj / down (fragment path: of QKV too)
+  const size_t nqkv = (size_t)(d.n_q_heads + 2 * d.n_kv_heads) * hd;
+  L.kpart = take(std::max((size_t)kMaxKsplit * max_rows * d.d_model,
+                          L.frag_rows ? kFragPartRows * std::max(nqkv, (size_t)d.d_model) : 0) * 4);
   L.kcnt_bytes = ks_cnt_bytes(d);
   L.kcnt = take(L.kcnt_bytes);  // their arrival counters (zero between kernels)
   L.mcnt_bytes = (size_t)d.n_layers * kMgReplicas * kKsCntStride * 4;
@@ -598,6 +659,10 @@ extern "C" laser_status laser_model_finalize(laser_model* m, int max_rows, void*
       return laser_fail(LASER_ERR_STATE, "layer %d has unset tensors", i);
   }
   Layout L = make_layout(d, max_rows);
+  if (bytes < L.total) {  // a workspace for forwards of max_rows rows only: prompts go in chunks of max_rows
+    const Layout narrow = make_layout(d, max_rows, false);
+    if (bytes >= narrow.total) L = narrow;
+  }
   if (!d_workspace || bytes < L.total) return laser_fail(LASER_ERR_INVALID_ARG, "workspace of %zu bytes needed", L.total);
   if (L.attn_part_bytes >= (1ull << 31))  // read by buffer instructions with 32-bit offsets
     return laser_fail(LASER_ERR_UNSUPPORTED, "attention partials of %zu bytes exceed 2 GiB", L.attn_part_bytes);
@@ -948,7 +1013,7 @@ static laser_status flush_pending(laser_kv* kv, laser_model* m, hipStream_t s, P
 // of all of them (each shared page is read once for every row), and each run keeps a group
 // of its own for its later pages.  A row's partials from the two are merged like any split.
 // The rows are reordered so that a family's runs are contiguous (outputs follow their rows).
-static void plan_groups(const laser_model* m, const laser_kv* kv, Plan& p) {
+static void plan_groups(const laser_model* m, const laser_kv* kv, Plan& p, int slot_cap) {
   const laser_model_desc& d = m->desc;
   const int G = d.n_q_heads / d.n_kv_heads;
   struct Run {
@@ -957,8 +1022,8 @@ static void plan_groups(const laser_model* m, const laser_kv* kv, Plan& p) {
   std::vector<Run> runs;
   for (int r = 0; r < p.M;) {
     int e = r + 1;
-    while (e < p.M && p.rows[e].seq == p.rows[r].seq) ++e;
-    runs.push_back({p.rows[r].seq, r, e, -1});
+    while (e < p.M && row_desc(&p, e).seq == row_desc(&p, r).seq) ++e;
+    runs.push_back({row_desc(&p, r).seq, r, e, -1});
     r = e;
   }
   struct Family {
@@ -1017,7 +1082,7 @@ static void plan_groups(const laser_model* m, const laser_kv* kv, Plan& p) {
   std::vector<int> row_prefix(p.M, -1), row_own(p.M, -1);
   auto add_group = [&](int seq, int r0, int r1, int pbeg, bool prefix) {
     int maxpos = 0;
-    for (int q = r0; q < r1; ++q) maxpos = std::max(maxpos, p.rows[q].pos);
+    for (int q = r0; q < r1; ++q) maxpos = std::max(maxpos, row_desc(&p, q).pos);
     const int gi = p.n_groups++;
     GroupDesc& g = p.groups[gi];
     g.seq = seq;
@@ -1037,7 +1102,10 @@ static void plan_groups(const laser_model* m, const laser_kv* kv, Plan& p) {
       const int gi = add_group(runs[f.members[0]].seq, runs[f.members[0]].r0, runs[f.members.back()].r1, 0, true);
       p.groups[gi].npages = f.shared;
     }
-    for (int k : f.members) add_group(runs[k].seq, runs[k].r0, runs[k].r1, f.shared, false);  // own pages
+    // own pages; the rows of a wide prefill in groups of kMaxRows, each over the pages its rows see
+    for (int k : f.members)
+      for (int r0 = runs[k].r0; r0 < runs[k].r1; r0 += kMaxRows)
+        add_group(runs[k].seq, r0, std::min(r0 + kMaxRows, runs[k].r1), f.shared, false);
   }
   // A work item (workgroup) takes one 16-column query tile of a group and spreads a split of
   // its pages over its 4 waves.  Splits of at most kMaxPagesPerWave pages per wave, enough
@@ -1052,6 +1120,12 @@ static void plan_groups(const laser_model* m, const laser_kv* kv, Plan& p) {
     units += (long long)(p.groups[i].npages - p.groups[i].pbeg) * d.n_kv_heads * ntiles(p.groups[i]);
   constexpr int kOwnSlots = 8;
   int base = std::min(kMaxPagesPerWave, std::max(1, (int)((units + kTargetAttnWaves - 1) / kTargetAttnWaves)));
+  if (p.M > kMaxRows) {  // a wide prefill: its many query tiles fill the chip by themselves, so long
+                         // runs, whose partials (rows x splits) cost more than they would gain
+    long long wgs = 0;
+    for (int i = 0; i < p.n_groups; ++i) wgs += (long long)ntiles(p.groups[i]) * d.n_kv_heads;
+    base = 2 * wgs >= m->cus ? kWidePagesPerWave : std::min(kWidePagesPerWave, std::max(base, (int)(units / kTargetAttnWaves)));
+  }
   auto item_count = [&]() {
     int n = 0;
     for (int i = 0; i < p.n_groups; ++i) {
@@ -1069,10 +1143,11 @@ static void plan_groups(const laser_model* m, const laser_kv* kv, Plan& p) {
       const bool shares = row_prefix[g.row0] >= 0;
       const bool is_prefix = row_prefix[g.row0] == i;
       const int max_wg = fusable(g) ? m->attn_fuse_max
-                                    : is_prefix ? kAttnMaxWG - kOwnSlots : (shares ? kOwnSlots : kAttnMaxWG);
+                                    : is_prefix ? kAttnMaxWG - kOwnSlots : (shares ? kOwnSlots : slot_cap);
       const int npg = g.npages - g.pbeg;
       g.pps = std::max(base, ceil_div(npg, max_wg * kAttnWaves));
       g.nwg = ceil_div(npg, kAttnWaves * g.pps);
+      g.pps = ceil_div(npg, kAttnWaves * g.nwg);  // the same workgroups, their waves evenly filled
     }
     if (item_count() <= kMaxAttnItems) break;
   }
@@ -1085,7 +1160,7 @@ static void plan_groups(const laser_model* m, const laser_kv* kv, Plan& p) {
   }
   // (a fused row counts as written directly: the merge kernel skips it)
   for (int q = 0; q < p.M; ++q)
-    p.row_nslots[q] = p.groups[row_own[q]].fused
+    (q < kMaxRows ? p.row_nslots[q] : p.wide_nslots[q / kMaxRows]) = p.groups[row_own[q]].fused
                           ? 1
                           : p.groups[row_own[q]].nwg + (row_prefix[q] >= 0 ? p.groups[row_prefix[q]].nwg : 0);
 
@@ -1135,12 +1210,16 @@ struct Scratch {
   unsigned* attn_cnt;
   LmPart* lm_part;
   size_t part_bytes, ml_bytes;
-  int rows;
+  int rows, max_wg;  // rows the attention partials are laid out for, slots per row
+  char* xfrag;       // fragment path's normed activations (null: that path is not used)
 };
 
 // The model workspace's scratch (every entry point but laser_decode_step_static).
-static Scratch workspace_scratch(const laser_model* m) {
+// A prefill forward of more than max_rows rows lays the same partial buffer out for its rows,
+// with fewer slots each.
+static Scratch workspace_scratch(const laser_model* m, int M) {
   const Layout& L = m->lay;
+  const int rows = std::max(m->max_rows, M);
   return Scratch{m->wsp<float>(L.attn_part),
                  m->wsp<float>(L.attn_ml),
                  m->wsp<float>(L.kpart),
@@ -1149,7 +1228,7 @@ static Scratch workspace_scratch(const laser_model* m) {
                  L.qpart ? m->wsp<float>(L.qpart) : nullptr,
                  L.sqpart ? m->wsp<float>(L.sqpart) : nullptr,
                  m->wsp<unsigned>(L.attn_cnt), m->wsp<LmPart>(L.lm_part), L.attn_part_bytes, L.attn_ml_bytes,
-                 m->max_rows};
+                 rows, std::max(1, kAttnMaxWG * m->max_rows / rows), L.frag_rows ? m->wsp<char>(L.xfrag) : nullptr};
 }
 
 static laser_status launch_forward(laser_model* m, laser_kv* kv, const FwdKey& key, hipStream_t s, const Scratch& sc,
@@ -1160,8 +1239,8 @@ static laser_status launch_forward(laser_model* m, laser_kv* kv, const FwdKey& k
 // class is being timed).
 static laser_status run_forward(laser_model* m, laser_kv* kv, Plan& p, const PlanIO& io, hipStream_t s,
                                 bool allow_graph = true, const Scratch* sc_in = nullptr) {
-  const Scratch sc = sc_in ? *sc_in : workspace_scratch(m);
-  plan_groups(m, kv, p);
+  const Scratch sc = sc_in ? *sc_in : workspace_scratch(m, p.M);
+  plan_groups(m, kv, p, sc.max_wg);
   p.io = io;
   FwdKey key{};
   key.M = p.M;
@@ -1169,15 +1248,16 @@ static laser_status run_forward(laser_model* m, laser_kv* kv, Plan& p, const Pla
   int max_slots = 1;
   bool merge = false;
   for (int i = 0; i < p.n_groups; ++i) merge |= !p.groups[i].direct && !p.groups[i].fused;
-  for (int q = 0; q < p.M; ++q) max_slots = std::max(max_slots, p.row_nslots[q]);
+  for (int q = 0; q < p.M; ++q) max_slots = std::max(max_slots, q < kMaxRows ? p.row_nslots[q] : p.wide_nslots[q / kMaxRows]);
   // the merge's slot bound is rounded up so that a growing context keeps the same key for a
   // while (the merge reads the row's own count)
-  key.mslots = std::min(kAttnMaxWG, ceil_div(max_slots, 8) * 8);
+  key.mslots = std::min(sc.max_wg, ceil_div(max_slots, 8) * 8);
   key.merge = merge;
   const laser_model_desc& d = m->desc;
   key.mo = merge && sc.mcnt != nullptr && p.M <= kValuMaxRows && (d.head_dim == 64 || d.head_dim == 128) &&
            (m->oproj_merge == 2 ||
             (m->oproj_merge == 1 && (size_t)d.d_model * d.n_q_heads * d.head_dim * m->es >= kMergeMinOBytes));
+  key.frag = sc.xfrag != nullptr && m->gemm_kernel == 0 && p.M >= kFragMinRows;
   key.kv_id = kv->id;
   // The merge in the O-projection's launch: every layer's counter grows by the forward's
   // merge workgroups, and the O-projection waits for the running total.  After a forward that
@@ -1302,10 +1382,15 @@ static laser_status launch_forward(laser_model* m, laser_kv* kv, const FwdKey& k
   const Plan* dp = m->wsp<Plan>(L.plans);
   laser_status st = LASER_OK;
   float* h = m->wsp<float>(L.h);
+  float* row_scale = m->wsp<float>(L.row_scale);  // (fragment path)
   HIP_TRY(timed(m, LASER_K_EMBED, s, [&] {  // the plan copy (from the staging slot hp), then the embedding gather
     const hipError_t e = launch_plan_fetch(hp, m->wsp<Plan>(L.plans), s);
     return e == hipSuccess ? launch_embed(dt, dp, key.M, m->embed, d.d_model, d.vocab, h, kv->bt, max_pps, s) : e;
   }));
+  if (key.frag)
+    HIP_TRY(timed(m, LASER_K_OTHER, s, [&] {
+      return launch_resid_norm(h, nullptr, 0, key.M, d.d_model, m->layers[0].attn_norm, d.rms_eps, sc.xfrag, row_scale, s);
+    }));
 
   GemmArgs base{};
   base.plan = dp;
@@ -1371,6 +1456,32 @@ static laser_status launch_forward(laser_model* m, laser_kv* kv, const FwdKey& k
     return LASER_OK;
   };
 
+  // Fragment path: the projection, and for the residual ones the sum of its K shares into h with
+  // the next projection's norm (next_gain; null: none follows in this forward's layers).
+  auto frag_gemm = [&](int cls, int epi, GemmArgs a, const void* x, int K, int N, int groups, const char* tile,
+                       const void* next_gain) -> laser_status {
+    const FragShape fs = frag_shape(epi, groups, key.M, K, m->cus);
+    a.K = K;
+    a.N = N;
+    a.M = key.M;
+    a.n_groups = groups;
+    a.afrag = (const char*)x;
+    a.frag_out = (char*)a.act;
+    a.row_scale = row_scale;
+    a.tsteps = K / 32;
+    a.wtile = m->tiles_on ? tile : nullptr;
+    a.ksplit = fs.ks;
+    a.kpart = sc.kpart;
+    HIP_TRY(timed(m, cls, s, [&] {
+      hipError_t e = launch_gemm_frag(epi, fs.cfg, a, s);
+      if (e == hipSuccess && epi == EPI_QKV) e = launch_qkv_epi(a, sc.kpart, nullptr, fs.ks, s);
+      if (e == hipSuccess && epi == EPI_RESID)
+        e = launch_resid_norm(h, sc.kpart, fs.ks, key.M, d.d_model, next_gain, d.rms_eps, sc.xfrag, row_scale, s);
+      return e;
+    }));
+    return LASER_OK;
+  };
+
   AttnArgs aa{};
   aa.plan = dp;
   aa.q = m->wsp<float>(L.q);
@@ -1384,6 +1495,8 @@ static laser_status launch_forward(laser_model* m, laser_kv* kv, const FwdKey& k
   aa.hkv = d.n_kv_heads;
   aa.G = G;
   aa.max_rows = sc.rows;
+  aa.max_wg = sc.max_wg;
+  aa.ofrag = key.frag ? m->wsp<char>(L.o) : nullptr;
   aa.scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)hd));
   aa.part = sc.attn_part;
   aa.ml = sc.attn_ml;
@@ -1406,8 +1519,9 @@ static laser_status launch_forward(laser_model* m, laser_kv* kv, const FwdKey& k
     a.gain = W.attn_norm;
     a.layer = li;
     const laser_model::Tiles* T = m->tiles_on ? &m->tiles[li] : nullptr;
-    st = gemm(LASER_K_QKV, EPI_QKV, a, d.d_model, (d.n_q_heads + 2 * d.n_kv_heads) * hd,
-              (d.n_q_heads + 2 * d.n_kv_heads) * hd, key.M, T ? T->qkv : nullptr);
+    const int nqkv = (d.n_q_heads + 2 * d.n_kv_heads) * hd;
+    st = key.frag ? frag_gemm(LASER_K_QKV, EPI_QKV, a, sc.xfrag, d.d_model, nqkv, nqkv / 16, T ? T->qkv : nullptr, nullptr)
+                  : gemm(LASER_K_QKV, EPI_QKV, a, d.d_model, nqkv, nqkv, key.M, T ? T->qkv : nullptr);
     if (st != LASER_OK) return st;
 
     aa.layer = li;
@@ -1435,8 +1549,10 @@ static laser_status launch_forward(laser_model* m, laser_kv* kv, const FwdKey& k
       mg.nslots = key.mslots;
       mg.nwg = key.M * d.n_q_heads;
     }
-    st = gemm(LASER_K_OPROJ, EPI_RESID, a, d.n_q_heads * hd, d.d_model, d.d_model, key.M, T ? T->o : nullptr,
-              key.mo ? &mg : nullptr);
+    st = key.frag ? frag_gemm(LASER_K_OPROJ, EPI_RESID, a, aa.ofrag, d.n_q_heads * hd, d.d_model, d.d_model / 16,
+                              T ? T->o : nullptr, W.mlp_norm)
+                  : gemm(LASER_K_OPROJ, EPI_RESID, a, d.n_q_heads * hd, d.d_model, d.d_model, key.M, T ? T->o : nullptr,
+                         key.mo ? &mg : nullptr);
     if (st != LASER_OK) return st;
 
     a = base;
@@ -1445,7 +1561,9 @@ static laser_status launch_forward(laser_model* m, laser_kv* kv, const FwdKey& k
     a.x = h;
     a.ldx = d.d_model;
     a.gain = W.mlp_norm;
-    st = gemm(LASER_K_GATEUP, EPI_SWIGLU, a, d.d_model, 2 * d.d_ffn, 2 * d.d_ffn, key.M, T ? T->gu : nullptr);
+    st = key.frag ? frag_gemm(LASER_K_GATEUP, EPI_SWIGLU, a, sc.xfrag, d.d_model, 2 * d.d_ffn, d.d_ffn / 8,
+                              T ? T->gu : nullptr, nullptr)
+                  : gemm(LASER_K_GATEUP, EPI_SWIGLU, a, d.d_model, 2 * d.d_ffn, 2 * d.d_ffn, key.M, T ? T->gu : nullptr);
     if (st != LASER_OK) return st;
 
     a = base;
@@ -1453,7 +1571,9 @@ static laser_status launch_forward(laser_model* m, laser_kv* kv, const FwdKey& k
     a.x = m->wsp<float>(L.act);
     a.ldx = d.d_ffn;
     a.gain = nullptr;
-    st = gemm(LASER_K_DOWN, EPI_RESID, a, d.d_ffn, d.d_model, d.d_model, key.M, T ? T->down : nullptr);
+    st = key.frag ? frag_gemm(LASER_K_DOWN, EPI_RESID, a, a.x, d.d_ffn, d.d_model, d.d_model / 16, T ? T->down : nullptr,
+                              li + 1 < d.n_layers ? m->layers[li + 1].attn_norm : nullptr)
+                  : gemm(LASER_K_DOWN, EPI_RESID, a, d.d_ffn, d.d_model, d.d_model, key.M, T ? T->down : nullptr);
     if (st != LASER_OK) return st;
   }
   if (key.n_out > 0) {
@@ -1622,7 +1742,7 @@ extern "C" laser_status laser_decode_step_static(laser_model* m, laser_kv* kv, i
   char* base = (char*)m->static_scratch;
   const Scratch sc{(float*)(base + o_part), (float*)(base + o_ml), (float*)(base + o_kpart), (unsigned*)(base + o_kcnt),
                    nullptr /* the merge kernel */, nullptr, nullptr,
-                   (unsigned*)(base + o_cnt), (LmPart*)(base + o_lm), part_bytes, ml_bytes, batch};
+                   (unsigned*)(base + o_cnt), (LmPart*)(base + o_lm), part_bytes, ml_bytes, batch, kAttnMaxWG, nullptr};
   std::vector<int> seqs(seq_ids, seq_ids + batch), grow(batch, 1);
   st = check_growth(m, kv, seqs, grow);
   if (st != LASER_OK) return st;
@@ -1667,14 +1787,17 @@ extern "C" laser_status laser_prefill(laser_model* m, laser_kv* kv, int seq_id, 
   if (st != LASER_OK) return st;
   Plan* p = new (std::nothrow) Plan;
   if (!p) return laser_fail(LASER_ERR_INVALID_ARG, "allocation failed");
-  for (int c0 = 0; c0 < n && st == LASER_OK; c0 += m->max_rows) {
-    const int M = std::min(m->max_rows, n - c0);
+  // (the row-major / row-wave kernel choices of set_gemm_kernel run max_rows rows at most)
+  const int chunk = m->lay.frag_rows && m->gemm_kernel == 0 ? std::max(m->max_rows, m->lay.frag_rows) : m->max_rows;
+  for (int c0 = 0, M; c0 < n && st == LASER_OK; c0 += M) {
+    M = std::min(chunk, n - c0);
+    if (M < kFragMinRows) M = std::min(M, m->max_rows);
     p->M = M;
     p->n_bt = 0;
     std::vector<PageUpdate> upd;
     const int pos0 = kv->pool.len(seq_id);
     kv->pool.append(seq_id, M, &upd);
-    for (int i = 0; i < M; ++i) p->rows[i] = RowDesc{seq_id, pos0 + i, 0, c0 + i};
+    for (int i = 0; i < std::min(M, kMaxRows); ++i) p->rows[i] = RowDesc{seq_id, pos0 + i, 0, c0 + i};  // (row_desc)
     push_updates(*p, upd);
     const bool last = c0 + M >= n;
     p->n_out = (last && d_logits_last) ? 1 : 0;

@@ -1,0 +1,123 @@
+"""Projections on matrix-core fragments (bf16 weights, forwards of 17 rows and more) and prompts
+prefilled in forwards of up to 512 rows.
+
+Prompts whose lengths sit at the edges of the path: 16/17 rows (where it begins), 64/65 (the
+first forward wider than the caller's rows can be), tile and row-block edges, 512/513 (one and
+two forwards), appended to an empty or a non-empty context, with callers' row limits from 1 to
+64.  Each prompt is checked against the float64 oracle (the last token's logits) and against the
+same library with the K-split kernel (laser_model_set_gemm_kernel mode 1), which runs it in
+chunks of the caller's rows: appended K/V within one rounding step of their storage type.
+Tolerances are the parity protocol's (gpu_helpers)."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_helpers import compare_logits, make_pair, require_gpu
+from oracle.transformer import SeqState
+from paper_2606_31580_amd import laser as L
+from paper_2606_31580_amd import synth
+from paper_2606_31580_amd.configs import ModelShape
+
+pytestmark = pytest.mark.gpu
+
+HD64 = ModelShape("frag-hd64", 2, 256, 4, 2, 64, 352, 515, False, False, "bf16", 1.0e4, 1.0e-5)
+HD128 = ModelShape("frag-hd128", 2, 384, 6, 2, 128, 1056, 1030, True, True, "bf16", 1.0e4, 1.0e-6)
+FP8 = ModelShape("frag-fp8", 2, 384, 6, 2, 128, 1056, 1030, True, True, "bf16", 1.0e4, 1.0e-6, "fp8")
+
+
+def _prefill(model, shape, kv, seq, prompt):
+    lg = torch.zeros(shape.vocab, device="cuda")
+    L.laser_prefill(model, kv, seq, prompt, lg)
+    torch.cuda.synchronize()
+    n = kv.seq_len(seq)
+    dt = torch.float8_e4m3fn if shape.kv_storage == "fp8" else torch.bfloat16
+    K = torch.empty((shape.n_layers, n, shape.n_kv_heads, shape.head_dim), dtype=dt, device="cuda")
+    V = torch.empty_like(K)
+    kv.export_kv(seq, K, V)
+    torch.cuda.synchronize()
+    return lg, K.float(), V.float()
+
+
+@pytest.mark.parametrize("shape,max_rows,ctx,lengths", [
+    (HD64, 64, 0, [16, 17, 32, 33, 64, 65, 129, 257]),
+    (HD64, 1, 5, [1, 17, 80, 512, 513, 529]),
+    (HD128, 16, 0, [17, 63, 97, 203, 300]),
+    (HD128, 64, 37, [48, 49, 112, 161, 511, 520]),
+    (FP8, 32, 250, [18, 40, 130]),
+], ids=lambda v: v.name if isinstance(v, ModelShape) else None)
+def test_prefill_edges(shape, max_rows, ctx, lengths):
+    require_gpu()
+    max_pos = 1024
+    model, orc, _ = make_pair(shape, max_rows=max_rows, max_positions=max_pos, cache_oracle=True)
+    k0, v0 = synth.make_prefill_kv(shape, ctx, 3) if ctx else (None, None)
+    toks = synth.make_tokens(max(lengths), shape.vocab, 3007)
+    st = SeqState.from_prefill(shape, synth.to_numpy(k0), synth.to_numpy(v0), max_pos) if ctx else SeqState(shape, max_pos)
+    refs = {}
+    for i, t in enumerate(toks):
+        refs[i + 1] = orc.decode_token(st, int(t))
+    # spacing of the storage type's values in [2^e, 2^(e+1)): 2^(e-7) for bf16 (8 significand bits),
+    # 2^(e-3) for E4M3 (4), so neighbours differ by at most that fraction of the larger one
+    step = 2.0 ** -3 if shape.kv_storage == "fp8" else 2.0 ** -7
+    for n in lengths:
+        got = {}
+        for mode in (0, 1):
+            model.set_gemm_kernel(mode)
+            kv = L.KVCache(model, 2 * (max_pos // 16), 2, max_pos // 16, poison=True)
+            kv.add_seq(0, ctx)
+            if ctx:
+                kv.import_kv(0, k0.cuda(), v0.cuda())
+            got[mode] = _prefill(model, shape, kv, 0, toks[:n].cuda())
+            kv.destroy()
+        model.set_gemm_kernel(0)
+        compare_logits(got[0][0].cpu().numpy(), refs[n], f"{shape.name} {n} tokens after {ctx}, max_rows {max_rows}")
+        for a, b in zip(got[0][1:], got[1][1:]):
+            assert torch.isfinite(a).all()
+            lim = step * torch.maximum(torch.maximum(a.abs(), b.abs()), b.square().mean().sqrt())
+            worst = float(((a - b).abs() / lim).max())
+            assert worst <= 1.0, f"{shape.name} {n} tokens: appended K/V differ by {worst} rounding steps"
+    model.destroy()
+
+
+def test_probe_batches_and_mixed_steps():
+    # probe chunks of 17-60 rows and mixed steps against the K-split kernel, with and without tiles
+    # (bitwise), replayed from graphs with eager work in between
+    require_gpu()
+    shape = HD128
+    w = {k: v.cuda() for k, v in synth.make_weights(shape).items()}
+    w["final_norm"].fill_(8.0)
+    model = L.Model(shape, w, max_rows=64, max_positions=1024, poison=True)
+    suffix = synth.make_suffix(8, shape.vocab).cuda()
+    for lens in ([300, 17, 45], [100, 16, 31, 250, 77, 400, 64], [50, 60, 70, 80]):
+        B = len(lens)
+        out = {}
+        for mode, tiles in ((0, True), (0, False), (1, True)):
+            model.set_gemm_kernel(mode)
+            model.set_tiles(tiles)
+            kv = L.KVCache(model, 256, B, 64, poison=True)
+            for i, n in enumerate(lens):
+                kv.add_seq(i, n)
+                kv.import_kv(i, *synth.make_prefill_kv(shape, n, 90 + i, device="cuda"))
+            lg = torch.zeros(B * 4, shape.vocab, device="cuda")
+            conf, arg = torch.zeros(B, device="cuda"), torch.zeros(B * 4, dtype=torch.int32, device="cuda")
+            reps = []
+            for _ in range(3):
+                L.laser_probe_confidence(model, kv, list(range(B)), suffix, 4, conf, arg, lg)
+                torch.cuda.synchronize()
+                reps.append((lg.clone(), conf.clone()))
+                torch.zeros(1000, device="cuda").sum().item()
+            for r in reps[1:]:
+                assert torch.equal(r[0], reps[0][0]) and torch.equal(r[1], reps[0][1])
+            tok = synth.make_tokens(B, shape.vocab, 83).cuda()
+            nxt, p = torch.zeros(B, dtype=torch.int32, device="cuda"), torch.zeros(B, device="cuda")
+            idx = list(range(0, B, 2))
+            c2, a2 = torch.zeros(len(idx), device="cuda"), torch.zeros(len(idx) * 4, dtype=torch.int32, device="cuda")
+            L.laser_step_mixed(model, kv, list(range(B)), tok, nxt, p, idx, suffix, 4, c2, a2)
+            torch.cuda.synchronize()
+            out[mode, tiles] = (reps[0][0], reps[0][1], p.clone(), c2.clone())
+            kv.destroy()
+        for a, b in zip(out[0, True], out[0, False]):
+            assert torch.equal(a, b), "tiles change the results"
+        first = out[0, True][0].view(B, 4, -1)[:, 0], out[1, True][0].view(B, 4, -1)[:, 0]  # (later rows follow their own tokens)
+        assert float((first[0] - first[1]).abs().max()) <= 2e-2
+        np.testing.assert_allclose(out[0, True][2].cpu(), out[1, True][2].cpu(), rtol=4e-2)
+    model.destroy()
