@@ -37,7 +37,7 @@ HIP_FLAGS = [
 # beside 40 matrix-core instructions).  Other files' kernels measured no gain or a loss (3-tile
 # K-split kernel: a 37-row prefill 0.986 -> 1.032 ms).
 MFMA_VGPR = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
-EXTRA_FLAGS = {"gemm_frag.hip": MFMA_VGPR}
+EXTRA_FLAGS = {"gemm_frag.hip": MFMA_VGPR, "attn.hip": MFMA_VGPR}
 C_FLAGS = ["-O2", "-fPIC", "-std=c99", "-Wall", "-ffp-contract=off", f"-I{INCLUDE}", f"-I{CSRC}"]
 
 

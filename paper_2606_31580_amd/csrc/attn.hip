@@ -28,32 +28,49 @@ namespace laser {
 
 __device__ __forceinline__ float safe_exp2(float x) { return x == -INFINITY ? 0.f : exp2f(x); }
 
-template <class KT, int HD>
+// Uniform loads of data written by earlier kernels, through the scalar unit: they don't count
+// against the vector-memory counter, which the page copies are waited for by.
+typedef int i32x8 __attribute__((ext_vector_type(8), aligned(16)));
+template <class T>
+__device__ __forceinline__ T ld_scalar(const void* p) {
+  return *(const __attribute__((address_space(4))) T*)(uint64_t)p;
+}
+
+// RING: runs of any length (see the page copies below); else every run has at most two pages
+// (batch 1, 14k positions, 7B: 9.0 us; the ring's detour through LDS costs 0.4-0.8 us there).
+template <class KT, int HD, bool RING>
 __global__ __launch_bounds__(64 * kAttnWaves) void k_attn(AttnArgs a) {
   constexpr int NS = HD / 32;  // QK k-steps
   constexpr int ND = HD / 16;  // PV d-tiles
   constexpr int NC = 16;       // query columns of the tile
-  // LDS: the tile's queries (bf16 hi/lo) and the merge slots of waves 1-3.  Rows are padded by 16 bytes, so the 16 columns a wave reads at
-  // once (row stride) fall in 16 different bank groups instead of one.
-  constexpr int QS = HD + 8;  // query row stride (bf16 elements)
-  constexpr int OS = HD + 4;  // merge-slot row stride (floats)
-  __shared__ __align__(16) uint16_t s_qh[NC * QS];
-  __shared__ __align__(16) uint16_t s_ql[NC * QS];
-  __shared__ __align__(16) float s_of[3 * 16 * OS];  // slot k at s_of + k * 16 * OS
-  __shared__ int s_pos[NC];
+  constexpr int OS = HD + 4;   // merge-slot row stride (floats; padded so that 16 rows fall in different bank groups)
+  constexpr int PB = 16 * HD * (int)sizeof(KT);  // bytes of a page's K (or V) block
+  constexpr int RBYTES = 4 * PB;                 // a wave's two pages, K and V of each
+  constexpr int QS = HD + 8;                     // query row stride (bf16 elements; padded likewise), short runs
+  constexpr int QB = RING ? NC * HD * 4 : 4 * NC * QS;  // the tile's queries: fp32, or bf16 hi rows, then lo rows
+  constexpr int MB = 3 * 16 * OS * 4;            // merge slots of waves 1-3 (after the pages)
+  constexpr int USED = RING ? QB + kAttnWaves * RBYTES : QB;
+  constexpr int SMEM = USED > MB ? USED : MB;
+  __shared__ __align__(16) char smem[SMEM];
   __shared__ float s_m[3][16];
   __shared__ float s_l[3][16];
 
-  const AttnItem wi = a.plan->items[blockIdx.x];
+  static_assert(sizeof(AttnItem) == 32, "one 32-byte load");
+  AttnItem wi;
+  if constexpr (RING)
+    wi = __builtin_bit_cast(AttnItem, ld_scalar<i32x8>(&a.plan->items[blockIdx.x]));
+  else
+    wi = a.plan->items[blockIdx.x];
   if (wi.nrows == 0) return;  // padding item
   const int nrows = wi.nrows & 0xff;
   const int fuse_n = (wi.nrows >> 8) & 0xff;  // fused group: its split count (else 0)
   const int NQ = nrows * a.G;
   const int kvh = blockIdx.y;
   const int tid = threadIdx.x;
-  const int w = tid >> 6, l = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
   const int lc = l & 15, lg = l >> 4;
   const int col0 = (wi.info & 0xff) * 16;  // the tile's first query column
+  const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
 
   // Wave w walks its run of the item's pages for the tile's 16 columns, then the waves merge
   // through LDS.
@@ -66,80 +83,89 @@ __global__ __launch_bounds__(64 * kAttnWaves) void k_attn(AttnArgs a) {
   const int p1 = min(p0 + wi.pps, wi.pend);
   const int* btrow = a.bt + (size_t)wi.seq * a.max_pps;
   const size_t layer_base = (size_t)a.layer * a.num_pages;
-  const size_t blk_elems = (size_t)16 * HD;
 
-  // The page ids of this wave's run are read up front, together with the queries, so no
-  // page load waits behind another page's data (vector-memory counters complete in order).
-  // (Named values, not an array: an indexed array goes to scratch memory, whose accesses
-  // share the in-order counter with the page loads.)
-  const int plast = max(p1 - 1, 0);  // clamped, branch-free: the loads issue back to back
-  const int pid0 = btrow[min(p0, plast)], pid1 = btrow[min(p0 + 1, plast)];
-  const int pid2 = btrow[min(p0 + 2, plast)], pid3 = btrow[min(p0 + 3, plast)];
-  auto page_id = [&](int pg) -> int {  // pg is wave-uniform
-    const int k = pg - p0;
-    return k == 0 ? pid0 : k == 1 ? pid1 : k == 2 ? pid2 : k == 3 ? pid3 : btrow[pg];
-  };
+  const int c = col0 + lc;           // this lane's query column
+  const int plast = max(p1 - 1, 0);  // clamped: a short run reads its last page again, unused
+  int pidA, pidB, cpos = -1;         // the first pages; the column's position (-1 past the group's columns)
+  // Short runs: the page ids and the queries load together (no page load waits behind another
+  // page's data), then the pages, straight into registers.
   constexpr int Q4 = NC * HD / 4 / (64 * kAttnWaves);  // query float4 loads per thread
   static_assert(Q4 * 4 * 64 * kAttnWaves == NC * HD, "query tile");
   float4 qv[Q4];
+  // Long runs: the queries go first, as they are, into LDS (they were just written by other XCDs:
+  // behind the page traffic they would arrive last): chunk k (16 bytes) of column j at place k ^ j
+  // of its row, so that the 16 columns a wave reads at once fall in 16 bank groups.  Columns past
+  // the group's read its last one (masked by their position).
+  constexpr int CPC = HD / 4, CPI = 64 / CPC;  // chunks per column, columns per copy
+  if constexpr (RING) {
 #pragma unroll
-  for (int i = 0; i < Q4; ++i) {  // padding columns load the last real one, zeroed when staged
-    const int idx = 4 * (tid + i * 64 * kAttnWaves);
-    const int c = min(col0 + idx / HD, NQ - 1), d = idx % HD;
-    const int row = wi.row0 + c / a.G;
-    const int head = kvh * a.G + c % a.G;
-    qv[i] = *(const float4*)(a.q + ((size_t)row * a.hq + head) * HD + d);
+    for (int i = 0; i < NC / CPI / kAttnWaves; ++i) {
+      const int j = (i * kAttnWaves + w) * CPI + l / CPC, k = (l % CPC) ^ j;
+      const int q = min(col0 + j, NQ - 1);
+      const float* src = a.q + ((size_t)(wi.row0 + q / a.G) * a.hq + kvh * a.G + q % a.G) * HD + 4 * k;
+      copy_to_lds16<false>((const char*)src, lds0 + (i * kAttnWaves + w) * 1024);
+    }
+    pidA = ld_scalar<int>(btrow + min(p0, plast));
+    pidB = ld_scalar<int>(btrow + min(p0 + 1, plast));
+    cpos = row_desc(a.plan, wi.row0 + min(c, NQ - 1) / a.G).pos;
+    asm volatile("" : "+v"(cpos));  // waited for here, the queries too, before the page copies are in flight
+    if (c >= NQ) cpos = -1;
+  } else {
+    // (vector loads: two scalar ones would wait for each other)
+    const int pv = wi.p0 + (tid >> 6) * wi.pps, lv = max(min(pv + wi.pps, wi.pend) - 1, 0);
+    pidA = btrow[min(pv, lv)];
+    pidB = btrow[min(pv + 1, lv)];
+#pragma unroll
+    for (int i = 0; i < Q4; ++i) {
+      const int idx = 4 * (tid + i * 64 * kAttnWaves);
+      const int q = min(col0 + idx / HD, NQ - 1), d = idx % HD;
+      qv[i] = *(const float4*)(a.q + ((size_t)(wi.row0 + q / a.G) * a.hq + kvh * a.G + q % a.G) * HD + d);
+    }
+    cpos = row_desc(a.plan, wi.row0 + min(c, NQ - 1) / a.G).pos;
   }
-  static_assert(NC <= 64 * kAttnWaves, "one position per thread");
-  const int cpos_loaded = row_desc(a.plan, wi.row0 + min(col0 + tid, NQ - 1) / a.G).pos;  // column tid's position
 
-  // Page operands are loaded D pages ahead of their use into a ring of raw buffers (bf16
-  // bits; fp32 pools are split into bf16 hi/lo when used).  A decode split is usually two
-  // pages, so its whole run is in flight at once.
-  constexpr int D = 2;
-  constexpr int KW = sizeof(KT) == 4 ? 2 : 1;  // 16-byte K loads per k-step (fp8: one 8-byte load)
-  // raw page words per lane, sized to what each storage type loads (registers are what
-  // limits how many waves a CU holds)
+  // Long runs: pages go by pairs through the wave's own LDS ring (K and V of two pages, copied as
+  // they lie in memory): once a pair's operands are in registers the next pair's copies start, so a wave has
+  // 16 KB (bf16, head dim 128) in flight all the time.
+  const unsigned ring0 = lds0 + QB + w * RBYTES;
+  const char* ring = smem + QB + w * RBYTES;
+  auto copy_page = [&](int pid, int slot) {
+    const size_t blk = ((layer_base + pid) * a.hkv + kvh) * (size_t)PB + 16 * l;
+#pragma unroll
+    for (int u = 0; u < PB / 1024; ++u) {
+      copy_to_lds16<true>((const char*)a.kpool + blk + u * 1024, ring0 + slot * 2 * PB + u * 1024);
+      copy_to_lds16<true>((const char*)a.vpool + blk + u * 1024, ring0 + slot * 2 * PB + PB + u * 1024);
+    }
+  };
+  constexpr int KW = sizeof(KT) == 4 ? 2 : 1;  // 16-byte K reads per k-step (fp8: one 8-byte read)
   using KRaw = std::conditional_t<sizeof(KT) == 1, u32x2, u32x4>;
   using VRaw = std::conditional_t<sizeof(KT) == 1, uint32_t, std::conditional_t<sizeof(KT) == 2, u32x2, u32x4>>;
-  KRaw kraw[D][NS][KW];
-  VRaw vraw[D][ND];
-  auto load_page = [&](int pg, auto bufc) {
+  KRaw kraw[2][NS][KW];
+  VRaw vraw[2][ND];
+  auto read_page = [&](auto bufc) {  // this lane's words of the page in a ring slot
     constexpr int buf = decltype(bufc)::value;
-    const int pid = page_id(pg);
-    const size_t blk = ((layer_base + pid) * a.hkv + kvh) * blk_elems;
-    if constexpr (sizeof(KT) == 1) {
-      const uint8_t* kb = (const uint8_t*)a.kpool + blk;
-      const uint8_t* vb = (const uint8_t*)a.vpool + blk;
+    const char* kb = ring + buf * 2 * PB;
+    const char* vb = kb + PB;
 #pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        const u32x2 t = ld_nt8(kb + s * 512 + 8 * l);
-        kraw[buf][s][0] = t;
-      }
+    for (int s = 0; s < NS; ++s)
 #pragma unroll
-      for (int dt = 0; dt < ND; ++dt)
-        vraw[buf][dt] = __builtin_nontemporal_load((const uint32_t*)(vb + dt * 256 + 4 * l));
-    } else if constexpr (sizeof(KT) == 2) {
-      const uint16_t* kb = (const uint16_t*)a.kpool + blk;
-      const uint16_t* vb = (const uint16_t*)a.vpool + blk;
+      for (int q = 0; q < KW; ++q) kraw[buf][s][q] = *(const KRaw*)(kb + (s * 512 + 8 * l) * sizeof(KT) + 16 * q);
 #pragma unroll
-      for (int s = 0; s < NS; ++s) kraw[buf][s][0] = ld_nt16(kb + s * 512 + 8 * l);
+    for (int dt = 0; dt < ND; ++dt) vraw[buf][dt] = *(const VRaw*)(vb + (dt * 256 + 4 * l) * sizeof(KT));
+  };
+  auto load_page = [&](int pid, auto bufc) {  // the same words straight from memory
+    constexpr int buf = decltype(bufc)::value;
+    const size_t blk = ((layer_base + pid) * a.hkv + kvh) * (size_t)PB;
+    const char* kb = (const char*)a.kpool + blk;
+    const char* vb = (const char*)a.vpool + blk;
 #pragma unroll
-      for (int dt = 0; dt < ND; ++dt) {
-        const u32x2 t = ld_nt8(vb + dt * 256 + 4 * l);
-        vraw[buf][dt] = t;
-      }
-    } else {
-      const float* kb = (const float*)a.kpool + blk;
-      const float* vb = (const float*)a.vpool + blk;
+    for (int s = 0; s < NS; ++s)
 #pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        kraw[buf][s][0] = ld_nt16(kb + s * 512 + 8 * l);
-        kraw[buf][s][KW - 1] = ld_nt16(kb + s * 512 + 8 * l + 4);
-      }
+      for (int q = 0; q < KW; ++q)
+        kraw[buf][s][q] = __builtin_nontemporal_load((global_ptr<KRaw>)(kb + (s * 512 + 8 * l) * sizeof(KT) + 16 * q));
 #pragma unroll
-      for (int dt = 0; dt < ND; ++dt) vraw[buf][dt] = ld_nt16(vb + dt * 256 + 4 * l);
-    }
+    for (int dt = 0; dt < ND; ++dt)
+      vraw[buf][dt] = __builtin_nontemporal_load((global_ptr<VRaw>)(vb + (dt * 256 + 4 * l) * sizeof(KT)));
   };
   // MFMA operands of one page.  K: lane l holds K[t = l%16][d = 32s + 8(l/16) + j];
   // V^T: V[t = 4(l/16) + j][d = 16dt + l%16].  Slots past the group's last position hold no
@@ -244,17 +270,32 @@ __global__ __launch_bounds__(64 * kAttnWaves) void k_attn(AttnArgs a) {
     }
   };
 
-  // The first D pages load unconditionally (a run shorter than D loads its last page again,
-  // unused): a branch here would make the wait for page 1's id also wait for page 0's data.
-  static_for<D>([&](auto b) { load_page(min(p0 + (int)b, plast), b); });
-  // Queries (loaded above, with the page ids) are split into bf16 hi/lo in LDS while the
-  // first pages are in flight.
-  {
+  bf16x8 qh[NS], ql[NS];
+  if constexpr (RING) {
+    copy_page(pidA, 0);
+    copy_page(pidB, 1);
+    wg_barrier();  // every wave's query copies had arrived before its page copies started
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const f32x4 x0 = *(const f32x4*)(smem + lc * HD * 4 + (((8 * s + 2 * lg) ^ lc) & (CPC - 1)) * 16);
+      const f32x4 x1 = *(const f32x4*)(smem + lc * HD * 4 + (((8 * s + 2 * lg + 1) ^ lc) & (CPC - 1)) * 16);
+      const float v[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
+      u32x4 hi, lo;
+      split8(v, hi, lo);
+      qh[s] = __builtin_bit_cast(bf16x8, hi);
+      ql[s] = __builtin_bit_cast(bf16x8, lo);
+    }
+  } else {
+    // Both pages load unconditionally: a branch here would make the wait for page 1's id also wait
+    // for page 0's data.  The queries are split into bf16 hi/lo in LDS meanwhile.
+    load_page(__builtin_amdgcn_readfirstlane(pidA), std::integral_constant<int, 0>{});
+    load_page(__builtin_amdgcn_readfirstlane(pidB), std::integral_constant<int, 1>{});
+    uint16_t* s_qh = (uint16_t*)smem;
+    uint16_t* s_ql = s_qh + NC * QS;
 #pragma unroll
     for (int i = 0; i < Q4; ++i) {
       const int idx = 4 * (tid + i * 64 * kAttnWaves);
-      const bool real = col0 + idx / HD < NQ;
-      const float x[4] = {real ? qv[i].x : 0.f, real ? qv[i].y : 0.f, real ? qv[i].z : 0.f, real ? qv[i].w : 0.f};
+      const float x[4] = {qv[i].x, qv[i].y, qv[i].z, qv[i].w};
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         uint16_t hi, lo;
@@ -263,19 +304,15 @@ __global__ __launch_bounds__(64 * kAttnWaves) void k_attn(AttnArgs a) {
         s_ql[(idx / HD) * QS + idx % HD + e] = lo;
       }
     }
-  }
-  if (tid < NC) s_pos[tid] = col0 + tid < NQ ? cpos_loaded : -1;
-  __syncthreads();
-
-  // pages in pairs: one max and one sum reduction across the lane groups per 32 positions
-  const int c = col0 + lc;  // this lane's query column
-  bf16x8 qh[NS], ql[NS];
+    asm volatile("" : "+v"(cpos));  // (issued ahead of the page loads, so it has arrived with the queries)
+    if (c >= NQ) cpos = -1;
+    __syncthreads();
 #pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    qh[s] = *(const bf16x8*)(s_qh + lc * QS + 32 * s + 8 * lg);
-    ql[s] = *(const bf16x8*)(s_ql + lc * QS + 32 * s + 8 * lg);
+    for (int s = 0; s < NS; ++s) {
+      qh[s] = *(const bf16x8*)(s_qh + lc * QS + 32 * s + 8 * lg);
+      ql[s] = *(const bf16x8*)(s_ql + lc * QS + 32 * s + 8 * lg);
+    }
   }
-  const int cpos = s_pos[lc];
   auto pair = [&](int pgA, auto ca, auto cbB) {
     const int pgB = pgA + 1;
     const bool hasB = pgB < p1;  // wave-uniform
@@ -319,17 +356,28 @@ __global__ __launch_bounds__(64 * kAttnWaves) void k_attn(AttnArgs a) {
     accumulate(A, pv, o);
     if (hasB) accumulate(B, pv + 4, o);
   };
-  for (int base = p0; base < p1; base += D) {
-    static_for<D / 2>([&](auto h) {
-      constexpr int bA = 2 * decltype(h)::value;
-      const int pg = base + bA;
-      if (pg < p1) {
-        pair(pg, std::integral_constant<int, bA>{}, std::integral_constant<int, bA + 1>{});
-        if (pg + D < p1) load_page(pg + D, std::integral_constant<int, bA>{});
-        if (pg + 1 + D < p1) load_page(pg + 1 + D, std::integral_constant<int, bA + 1>{});
+  // pages in pairs: one max and one sum reduction across the lane groups per 32 positions
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  if constexpr (RING) {
+    for (int pg = p0; pg < p1; pg += 2) {
+      const int nA = ld_scalar<int>(btrow + min(pg + 2, plast)), nB = ld_scalar<int>(btrow + min(pg + 3, plast));
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the pair has landed
+      read_page(I0{});
+      read_page(I1{});
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      if (pg + 2 < p1) {
+        copy_page(nA, 0);
+        copy_page(nB, 1);
       }
-    });
+      pair(pg, I0{}, I1{});
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (a wave without pages: its copies are done too)
+  } else if (p0 < p1) {
+    pair(p0, I0{}, I1{});
   }
+  wg_barrier();  // the queries' and the rings' LDS is free: merge slots
+  float* s_of = (float*)smem;
 
   // ---- one-round merge of the page-parallel waves: 1-3 publish, 0 absorbs in order
   if (w > 0) {
@@ -554,7 +602,8 @@ hipError_t launch_attn_merge(const AttnArgs& a, int M, int hd, int nslots, hipSt
 
 template <class KT, int HD>
 static hipError_t launch_hd(const AttnArgs& a, dim3 grid, hipStream_t s) {
-  return launch_k(k_attn<KT, HD>, grid, dim3(64 * kAttnWaves), s, a);
+  const dim3 block(64 * kAttnWaves);
+  return a.long_runs ? launch_k(k_attn<KT, HD, true>, grid, block, s, a) : launch_k(k_attn<KT, HD, false>, grid, block, s, a);
 }
 
 hipError_t launch_attn(int dtype, int hd, const AttnArgs& a, dim3 grid, hipStream_t s) {

@@ -140,6 +140,12 @@ __device__ __forceinline__ void copy_to_lds16(const char* g, unsigned lds) {
   else
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(g) : "memory");
 }
+// At most N of the wave's copies still in flight, its LDS reads done.
+template <int N>
+__device__ __forceinline__ void wait_copies() {
+  static_assert(N >= 0 && N < 64, "vmcnt");
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
+}
 // Workgroup barrier that waits for no copies in flight.
 __device__ __forceinline__ void wg_barrier() {
   asm volatile("" ::: "memory");

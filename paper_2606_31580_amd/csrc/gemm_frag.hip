@@ -27,13 +27,6 @@
 
 namespace laser {
 
-// At most N of the wave's copies still in flight, its LDS reads done.
-template <int N>
-__device__ __forceinline__ void wait_copies() {
-  static_assert(N >= 0 && N < 64, "vmcnt");
-  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
-}
-
 template <int EPI, int MTW, int NGW, int WM, int WN, int NS>
 __global__ __launch_bounds__(64 * WM * WN) void k_gemm_frag(GemmArgs a) {
   constexpr int W = WM * WN, MT = WM * MTW, NG = WN * NGW;

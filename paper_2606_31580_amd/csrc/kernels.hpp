@@ -174,6 +174,7 @@ struct AttnArgs {
   float* part;  // [hkv][max_wg][max_rows*G][hd]
   float* ml;    // [hkv][max_wg][max_rows*G][2]
   int max_wg;   // partial slots per (kv head, column): kAttnMaxWG, fewer when a wide prefill's rows share the buffer
+  int long_runs;  // some item's waves walk more than two pages
   char* ofrag;  // the output as fragments for the O-projection (null: fp32 rows in o)
   uint32_t part_bytes, ml_bytes;
   unsigned* cnt;  // fused groups' arrival counters [hkv][kMaxGroups] x kAttnCntStride; zero between kernels

@@ -81,6 +81,7 @@ constexpr int kTargetAttnWaves = LASER_ATTN_TARGET_WAVES;  // attention waves a 
 #define LASER_ATTN_MAX_PPS 4
 #endif
 constexpr int kMaxPagesPerWave = LASER_ATTN_MAX_PPS;
+constexpr int kLongestRun = 128;       // pages per wave, where longer runs save a round of workgroups
 constexpr int kWidePagesPerWave = 16;  // the same for prefill forwards of more than kMaxRows rows
 // Splits of a one-row group that merges inside the attention kernel: its last workgroup reads
 // every split's partial (G columns x (hd + 2) floats each), so fewer, longer splits shorten
@@ -110,10 +111,12 @@ struct FwdKey {
   int M, n_out, agx, mslots, merge;  // agx: attention work items (grid width)
   int mo;                              // the split merge runs in the O-projection's launch
   int frag;                            // the projections run on the fragment path (fixed by M)
+  int long_runs;                       // attention runs of more than two pages
   uint64_t kv_id;
   // same launches apart from the attention grid width
   bool same_shape(const FwdKey& o) const {
-    return M == o.M && n_out == o.n_out && mslots == o.mslots && merge == o.merge && mo == o.mo && kv_id == o.kv_id;
+    return M == o.M && n_out == o.n_out && mslots == o.mslots && merge == o.merge && mo == o.mo &&
+           long_runs == o.long_runs && kv_id == o.kv_id;
   }
 };
 
@@ -1126,6 +1129,22 @@ static void plan_groups(const laser_model* m, const laser_kv* kv, Plan& p, int s
     for (int i = 0; i < p.n_groups; ++i) wgs += (long long)ntiles(p.groups[i]) * d.n_kv_heads;
     base = 2 * wgs >= m->cus ? kWidePagesPerWave : std::min(kWidePagesPerWave, std::max(base, (int)(units / kTargetAttnWaves)));
   }
+  if (p.M <= kMaxRows) {
+    // Longer runs until every workgroup is resident at once: a workgroup keeps its pages streaming,
+    // so one round of long runs beats several rounds of short ones, each with its own start-up and
+    // partials (68k positions, batch 8, 8B: 63.5 us with runs of at most 4 pages, 52.9 with one
+    // round), and a last round that is nearly empty costs most (runs of 16 pages: 1.4 rounds, the
+    // step 840 against 800 us).
+    const int pos_bytes = d.head_dim * m->kv_es;  // a wave's ring takes 64 of these, of 160 KB per CU
+    const int resident = m->cus * (pos_bytes >= 512 ? 1 : pos_bytes >= 256 ? 2 : 3);
+    auto workgroups = [&](int b) {
+      long long n = 0;
+      for (int i = 0; i < p.n_groups; ++i)
+        n += (long long)ceil_div(p.groups[i].npages - p.groups[i].pbeg, kAttnWaves * b) * ntiles(p.groups[i]) * d.n_kv_heads;
+      return n;
+    };
+    while (base < kLongestRun && workgroups(base) > resident) ++base;
+  }
   auto item_count = [&]() {
     int n = 0;
     for (int i = 0; i < p.n_groups; ++i) {
@@ -1248,6 +1267,7 @@ static laser_status run_forward(laser_model* m, laser_kv* kv, Plan& p, const Pla
   int max_slots = 1;
   bool merge = false;
   for (int i = 0; i < p.n_groups; ++i) merge |= !p.groups[i].direct && !p.groups[i].fused;
+  for (int i = 0; i < p.n_groups; ++i) key.long_runs |= p.groups[i].pps > 2;
   for (int q = 0; q < p.M; ++q) max_slots = std::max(max_slots, q < kMaxRows ? p.row_nslots[q] : p.wide_nslots[q / kMaxRows]);
   // the merge's slot bound is rounded up so that a growing context keeps the same key for a
   // while (the merge reads the row's own count)
@@ -1496,6 +1516,7 @@ static laser_status launch_forward(laser_model* m, laser_kv* kv, const FwdKey& k
   aa.G = G;
   aa.max_rows = sc.rows;
   aa.max_wg = sc.max_wg;
+  aa.long_runs = key.long_runs;
   aa.ofrag = key.frag ? m->wsp<char>(L.o) : nullptr;
   aa.scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)hd));
   aa.part = sc.attn_part;
