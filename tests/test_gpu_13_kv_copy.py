@@ -1,0 +1,73 @@
+"""KV import and export against the pool layout that include/laser.h documents, byte for byte.
+
+Lengths that end inside a group of 4 positions, at page edges and past them; both head
+dimensions; fp32, bf16 and E4M3; dense arrays on 16-byte boundaries (the vectorised copy) and one
+element past them (the element-wise one).  Pool bytes of positions past the length keep what
+they held."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_helpers import require_gpu
+from paper_2606_31580_amd import laser as L
+from paper_2606_31580_amd import synth
+from paper_2606_31580_amd.configs import ModelShape
+
+pytestmark = pytest.mark.gpu
+
+
+def _shape(hd, hkv, kind):
+    dt = "f32" if kind == "f32" else "bf16"
+    return ModelShape(f"kv-{hd}-{hkv}-{kind}", 3, 192, 2 * hkv, hkv, hd, 64, 130, False, False, dt, 1.0e4, 1.0e-5,
+                      "fp8" if kind == "fp8" else "")
+
+
+def _expect(pool, dense, table, hd, is_k):
+    """pool [layers][pages][hkv][16 * hd] with the dense [layers][len][hkv][hd] values put in place."""
+    n = dense.shape[1]
+    for pos in range(n):
+        t, d = pos % 16, np.arange(hd)
+        off = (((d // 32 * 4 + d % 32 // 8) * 16 + t) * 8 + d % 8 if is_k
+               else ((d // 16 * 4 + t // 4) * 16 + d % 16) * 4 + t % 4)
+        pool[:, table[pos // 16], :, off] = dense[:, pos].transpose(2, 0, 1)
+
+
+@pytest.mark.parametrize("hd,hkv,kind", [(64, 2, "f32"), (128, 1, "f32"), (64, 3, "bf16"), (128, 4, "bf16"), (64, 1, "fp8"),
+                                         (128, 2, "fp8")])
+def test_import_export_layout(hd, hkv, kind):
+    require_gpu()
+    shape = _shape(hd, hkv, kind)
+    w = {k: v.cuda() for k, v in synth.make_weights(shape).items()}
+    model = L.Model(shape, w, max_rows=4, max_positions=512, tiles=False)
+    es, dt = {"f32": (4, np.uint32), "bf16": (2, np.uint16), "fp8": (1, np.uint8)}[kind]
+    rng = np.random.default_rng(5)
+    for n in (1, 3, 4, 6, 15, 16, 17, 18, 31, 32, 63, 250):
+        for shift in (0, 1):  # dense arrays that start `shift` elements past a 16-byte boundary
+            kv = L.KVCache(model, 40, 2, 32)
+            kv.k_pool.fill_(0xA5)
+            kv.v_pool.fill_(0x5A)
+            kv.add_seq(1, 20)  # the sequence under test does not start at page 0
+            kv.add_seq(0, n)
+            size = 3 * n * hkv * hd
+            raw = [rng.integers(0, 256, size * es, dtype=np.uint8) for _ in range(2)]
+            buf = [torch.zeros(size * es + 32, dtype=torch.uint8, device="cuda") for _ in range(2)]
+            dense = [b[shift * es: shift * es + size * es] for b in buf]
+            for d, r in zip(dense, raw):
+                d.copy_(torch.from_numpy(r))
+            views = [d.view(3, n, hkv, hd * es) for d in dense]
+            kv.import_kv(0, *views)
+            torch.cuda.synchronize()
+            table = kv.page_table(0)
+            for pool, fill, r, is_k in ((kv.k_pool, 0xA5, raw[0], True), (kv.v_pool, 0x5A, raw[1], False)):
+                want = np.full(pool.numel(), fill, dtype=np.uint8).view(dt).reshape(3, 40, hkv, 16 * hd).copy()
+                _expect(want, r.view(dt).reshape(3, n, hkv, hd), table, hd, is_k)
+                got = pool.cpu().numpy().view(dt).reshape(want.shape)
+                assert np.array_equal(got, want), f"{shape.name}: {n} positions, shift {shift}, {'K' if is_k else 'V'}"
+            back = [torch.full_like(b, 0xEE) for b in buf]
+            kv.export_kv(0, *[b[shift * es: shift * es + size * es].view(3, n, hkv, hd * es) for b in back])
+            torch.cuda.synchronize()
+            for b, r in zip(back, raw):
+                assert np.array_equal(b[shift * es: shift * es + size * es].cpu().numpy(), r)
+                assert bool((b[:shift * es] == 0xEE).all()) and bool((b[shift * es + size * es:] == 0xEE).all())
+            kv.destroy()
+    model.destroy()
