@@ -38,22 +38,25 @@ __device__ __forceinline__ T ld_scalar(const void* p) {
 
 // RING: runs of any length (see the page copies below); else every run has at most two pages
 // (batch 1, 14k positions, 7B: 9.0 us; the ring's detour through LDS costs 0.4-0.8 us there).
-template <class KT, int HD, bool RING>
+// NT: 16-column query tiles per item (2: every page serves both from one load; RING only).
+template <class KT, int HD, bool RING, int NT>
 __global__ __launch_bounds__(64 * kAttnWaves) void k_attn(AttnArgs a) {
   constexpr int NS = HD / 32;  // QK k-steps
   constexpr int ND = HD / 16;  // PV d-tiles
-  constexpr int NC = 16;       // query columns of the tile
+  constexpr int NC = 16 * NT;  // query columns of the item
+  static_assert(RING || NT == 1, "two tiles: long runs");
   constexpr int OS = HD + 4;   // merge-slot row stride (floats; padded so that 16 rows fall in different bank groups)
   constexpr int PB = 16 * HD * (int)sizeof(KT);  // bytes of a page's K (or V) block
   constexpr int RBYTES = 4 * PB;                 // a wave's two pages, K and V of each
   constexpr int QS = HD + 8;                     // query row stride (bf16 elements; padded likewise), short runs
   constexpr int QB = RING ? NC * HD * 4 : 4 * NC * QS;  // the tile's queries: fp32, or bf16 hi rows, then lo rows
-  constexpr int MB = 3 * 16 * OS * 4;            // merge slots of waves 1-3 (after the pages)
+  constexpr int MB = NT * 3 * 16 * OS * 4;       // merge slots of waves 1-3 (after the pages)
+  constexpr int ML = NT * 3 * 16 * 2 * 4 + 16;   // their (m, l), the fused merge's ticket
   constexpr int USED = RING ? QB + kAttnWaves * RBYTES : QB;
-  constexpr int SMEM = USED > MB ? USED : MB;
+  constexpr int SMEM = USED > MB + ML ? USED : MB + ML;
   __shared__ __align__(16) char smem[SMEM];
-  __shared__ float s_m[3][16];
-  __shared__ float s_l[3][16];
+  float* s_m = (float*)(smem + MB);  // [tile][wave - 1][column]
+  float* s_l = s_m + NT * 48;
 
   static_assert(sizeof(AttnItem) == 32, "one 32-byte load");
   AttnItem wi;
@@ -69,24 +72,30 @@ __global__ __launch_bounds__(64 * kAttnWaves) void k_attn(AttnArgs a) {
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
   const int lc = l & 15, lg = l >> 4;
-  const int col0 = (wi.info & 0xff) * 16;  // the tile's first query column
+  const int col0 = (wi.info & 0xff) * NC;  // the item's first query column
+  const bool two = NT == 2 && NQ - col0 > 16;  // it has a second tile
   const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
 
   // Wave w walks its run of the item's pages for the tile's 16 columns, then the waves merge
   // through LDS.
-  float m_run = -INFINITY, l_run = 0.f;
-  f32x4 o[ND];
+  float m_run[NT], l_run[NT];
+  f32x4 o[NT][ND];
 #pragma unroll
-  for (int dt = 0; dt < ND; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int u = 0; u < NT; ++u) {
+    m_run[u] = -INFINITY;
+    l_run[u] = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < ND; ++dt) o[u][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
 
   const int p0 = wi.p0 + w * wi.pps;
   const int p1 = min(p0 + wi.pps, wi.pend);
   const int* btrow = a.bt + (size_t)wi.seq * a.max_pps;
   const size_t layer_base = (size_t)a.layer * a.num_pages;
 
-  const int c = col0 + lc;           // this lane's query column
+  const int c = col0 + lc;           // this lane's query column (of the first tile)
   const int plast = max(p1 - 1, 0);  // clamped: a short run reads its last page again, unused
-  int pidA, pidB, cpos = -1;         // the first pages; the column's position (-1 past the group's columns)
+  int pidA, pidB, cpos[NT];          // the first pages; the columns' positions (-1 past the group's columns)
   // Short runs: the page ids and the queries load together (no page load waits behind another
   // page's data), then the pages, straight into registers.
   constexpr int Q4 = NC * HD / 4 / (64 * kAttnWaves);  // query float4 loads per thread
@@ -100,16 +109,20 @@ __global__ __launch_bounds__(64 * kAttnWaves) void k_attn(AttnArgs a) {
   if constexpr (RING) {
 #pragma unroll
     for (int i = 0; i < NC / CPI / kAttnWaves; ++i) {
-      const int j = (i * kAttnWaves + w) * CPI + l / CPC, k = (l % CPC) ^ j;
+      const int j = (i * kAttnWaves + w) * CPI + l / CPC, k = (l % CPC) ^ (j & 15);
       const int q = min(col0 + j, NQ - 1);
       const float* src = a.q + ((size_t)(wi.row0 + q / a.G) * a.hq + kvh * a.G + q % a.G) * HD + 4 * k;
       copy_to_lds16<false>((const char*)src, lds0 + (i * kAttnWaves + w) * 1024);
     }
     pidA = ld_scalar<int>(btrow + min(p0, plast));
     pidB = ld_scalar<int>(btrow + min(p0 + 1, plast));
-    cpos = row_desc(a.plan, wi.row0 + min(c, NQ - 1) / a.G).pos;
-    asm volatile("" : "+v"(cpos));  // waited for here, the queries too, before the page copies are in flight
-    if (c >= NQ) cpos = -1;
+#pragma unroll
+    for (int u = 0; u < NT; ++u) cpos[u] = row_desc(a.plan, wi.row0 + min(c + 16 * u, NQ - 1) / a.G).pos;
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {
+      asm volatile("" : "+v"(cpos[u]));  // waited for here, the queries too, before the page copies are in flight
+      if (c + 16 * u >= NQ) cpos[u] = -1;
+    }
   } else {
     // (vector loads: two scalar ones would wait for each other)
     const int pv = wi.p0 + (tid >> 6) * wi.pps, lv = max(min(pv + wi.pps, wi.pend) - 1, 0);
@@ -121,7 +134,7 @@ __global__ __launch_bounds__(64 * kAttnWaves) void k_attn(AttnArgs a) {
       const int q = min(col0 + idx / HD, NQ - 1), d = idx % HD;
       qv[i] = *(const float4*)(a.q + ((size_t)(wi.row0 + q / a.G) * a.hq + kvh * a.G + q % a.G) * HD + d);
     }
-    cpos = row_desc(a.plan, wi.row0 + min(c, NQ - 1) / a.G).pos;
+    cpos[0] = row_desc(a.plan, wi.row0 + min(c, NQ - 1) / a.G).pos;
   }
 
   // Long runs: pages go by pairs through the wave's own LDS ring (K and V of two pages, copied as
@@ -270,21 +283,24 @@ __global__ __launch_bounds__(64 * kAttnWaves) void k_attn(AttnArgs a) {
     }
   };
 
-  bf16x8 qh[NS], ql[NS];
+  bf16x8 qh[NT][NS], ql[NT][NS];
   if constexpr (RING) {
     copy_page(pidA, 0);
     copy_page(pidB, 1);
     wg_barrier();  // every wave's query copies had arrived before its page copies started
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      const f32x4 x0 = *(const f32x4*)(smem + lc * HD * 4 + (((8 * s + 2 * lg) ^ lc) & (CPC - 1)) * 16);
-      const f32x4 x1 = *(const f32x4*)(smem + lc * HD * 4 + (((8 * s + 2 * lg + 1) ^ lc) & (CPC - 1)) * 16);
-      const float v[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
-      u32x4 hi, lo;
-      split8(v, hi, lo);
-      qh[s] = __builtin_bit_cast(bf16x8, hi);
-      ql[s] = __builtin_bit_cast(bf16x8, lo);
-    }
+    for (int u = 0; u < NT; ++u)
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const char* qr = smem + (16 * u + lc) * HD * 4;
+        const f32x4 x0 = *(const f32x4*)(qr + (((8 * s + 2 * lg) ^ lc) & (CPC - 1)) * 16);
+        const f32x4 x1 = *(const f32x4*)(qr + (((8 * s + 2 * lg + 1) ^ lc) & (CPC - 1)) * 16);
+        const float v[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
+        u32x4 hi, lo;
+        split8(v, hi, lo);
+        qh[u][s] = __builtin_bit_cast(bf16x8, hi);
+        ql[u][s] = __builtin_bit_cast(bf16x8, lo);
+      }
   } else {
     // Both pages load unconditionally: a branch here would make the wait for page 1's id also wait
     // for page 0's data.  The queries are split into bf16 hi/lo in LDS meanwhile.
@@ -304,57 +320,69 @@ __global__ __launch_bounds__(64 * kAttnWaves) void k_attn(AttnArgs a) {
         s_ql[(idx / HD) * QS + idx % HD + e] = lo;
       }
     }
-    asm volatile("" : "+v"(cpos));  // (issued ahead of the page loads, so it has arrived with the queries)
-    if (c >= NQ) cpos = -1;
+    asm volatile("" : "+v"(cpos[0]));  // (issued ahead of the page loads, so it has arrived with the queries)
+    if (c >= NQ) cpos[0] = -1;
     __syncthreads();
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-      qh[s] = *(const bf16x8*)(s_qh + lc * QS + 32 * s + 8 * lg);
-      ql[s] = *(const bf16x8*)(s_ql + lc * QS + 32 * s + 8 * lg);
+      qh[0][s] = *(const bf16x8*)(s_qh + lc * QS + 32 * s + 8 * lg);
+      ql[0][s] = *(const bf16x8*)(s_ql + lc * QS + 32 * s + 8 * lg);
     }
   }
   auto pair = [&](int pgA, auto ca, auto cbB) {
     const int pgB = pgA + 1;
     const bool hasB = pgB < p1;  // wave-uniform
     PageOps A, B;
+    f32x4 sat[NT], sbt[NT];
     unpack(pgA, ca, A);
-    const f32x4 sa = scores(A, qh, ql);
-    f32x4 sb = f32x4{0.f, 0.f, 0.f, 0.f};
+    static_for<NT>([&](auto uc) {
+      constexpr int u = decltype(uc)::value;
+      sbt[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (u == 0 || two) sat[u] = scores(A, qh[u], ql[u]);
+    });
     if (hasB) {
       unpack(pgB, cbB, B);
-      sb = scores(B, qh, ql);
+      static_for<NT>([&](auto uc) {
+        constexpr int u = decltype(uc)::value;
+        if (u == 0 || two) sbt[u] = scores(B, qh[u], ql[u]);
+      });
     }
-    float sv[8];
-    float mloc = -INFINITY;
+    static_for<NT>([&](auto uc) {
+      constexpr int u = decltype(uc)::value;
+      if (u > 0 && !two) return;  // workgroup-uniform
+      const f32x4 sa = sat[u], sb = sbt[u];
+      float sv[8];
+      float mloc = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int ta = pgA * 16 + 4 * lg + i, tb = pgB * 16 + 4 * lg + i;
-      sv[i] = (ta <= cpos) ? sa[i] * a.scale_log2 : -INFINITY;
-      sv[4 + i] = (hasB && tb <= cpos) ? sb[i] * a.scale_log2 : -INFINITY;
-      mloc = fmaxf(mloc, fmaxf(sv[i], sv[4 + i]));
-    }
-    mloc = max_x16(mloc);
-    mloc = max_x32(mloc);
-    const float m_new = fmaxf(m_run, mloc);
-    // o and l are still zero while m_run is -inf, so they need no rescale then
-    const bool grow = m_run != -INFINITY && m_new != m_run;
-    const float alpha = grow ? __builtin_amdgcn_exp2f(m_run - m_new) : 1.f;
-    float pv[8], ls = 0.f;
+      for (int i = 0; i < 4; ++i) {
+        const int ta = pgA * 16 + 4 * lg + i, tb = pgB * 16 + 4 * lg + i;
+        sv[i] = (ta <= cpos[u]) ? sa[i] * a.scale_log2 : -INFINITY;
+        sv[4 + i] = (hasB && tb <= cpos[u]) ? sb[i] * a.scale_log2 : -INFINITY;
+        mloc = fmaxf(mloc, fmaxf(sv[i], sv[4 + i]));
+      }
+      mloc = max_x16(mloc);
+      mloc = max_x32(mloc);
+      const float m_new = fmaxf(m_run[u], mloc);
+      // o and l are still zero while m_run is -inf, so they need no rescale then
+      const bool grow = m_run[u] != -INFINITY && m_new != m_run[u];
+      const float alpha = grow ? __builtin_amdgcn_exp2f(m_run[u] - m_new) : 1.f;
+      float pv[8], ls = 0.f;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      pv[i] = (sv[i] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(sv[i] - m_new);
-      ls += pv[i];
-    }
-    ls = sum_x16(ls);
-    ls = sum_x32(ls);
-    l_run = l_run * alpha + ls;
-    m_run = m_new;
-    if (__builtin_amdgcn_read_exec() & __ballot(grow)) {  // any lane whose max moved
+      for (int i = 0; i < 8; ++i) {
+        pv[i] = (sv[i] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(sv[i] - m_new);
+        ls += pv[i];
+      }
+      ls = sum_x16(ls);
+      ls = sum_x32(ls);
+      l_run[u] = l_run[u] * alpha + ls;
+      m_run[u] = m_new;
+      if (__builtin_amdgcn_read_exec() & __ballot(grow)) {  // any lane whose max moved
 #pragma unroll
-      for (int dt = 0; dt < ND; ++dt) o[dt] *= alpha;
-    }
-    accumulate(A, pv, o);
-    if (hasB) accumulate(B, pv + 4, o);
+        for (int dt = 0; dt < ND; ++dt) o[u][dt] *= alpha;
+      }
+      accumulate(A, pv, o[u]);
+      if (hasB) accumulate(B, pv + 4, o[u]);
+    });
   };
   // pages in pairs: one max and one sum reduction across the lane groups per 32 positions
   using I0 = std::integral_constant<int, 0>;
@@ -381,66 +409,79 @@ __global__ __launch_bounds__(64 * kAttnWaves) void k_attn(AttnArgs a) {
 
   // ---- one-round merge of the page-parallel waves: 1-3 publish, 0 absorbs in order
   if (w > 0) {
+    static_for<NT>([&](auto uc) {
+      constexpr int u = decltype(uc)::value;
+      if (u > 0 && !two) return;
+      const int slot = u * 3 + w - 1;
 #pragma unroll
-    for (int dt = 0; dt < ND; ++dt) *(f32x4*)(s_of + (w - 1) * 16 * OS + lc * OS + 16 * dt + 4 * lg) = o[dt];
-    if (lg == 0) {
-      s_m[w - 1][lc] = m_run;
-      s_l[w - 1][lc] = l_run;
-    }
+      for (int dt = 0; dt < ND; ++dt) *(f32x4*)(s_of + slot * 16 * OS + lc * OS + 16 * dt + 4 * lg) = o[u][dt];
+      if (lg == 0) {
+        s_m[slot * 16 + lc] = m_run[u];
+        s_l[slot * 16 + lc] = l_run[u];
+      }
+    });
   }
   __syncthreads();
   if (w != 0 && fuse_n == 0) return;
   const size_t ncols = (size_t)a.max_rows * a.G;
   const __amdgpu_buffer_rsrc_t rpart = dev_rsrc(a.part, a.part_bytes), rml = dev_rsrc(a.ml, a.ml_bytes);
   if (w == 0) {
+    static_for<NT>([&](auto uc) {
+      constexpr int u = decltype(uc)::value;
+      if (u > 0 && !two) return;
+      float m = m_run[u], ls = l_run[u];
 #pragma unroll
-    for (int u = 0; u < 3; ++u) {
-      const float m2 = s_m[u][lc], l2 = s_l[u][lc];
-      const float mm = fmaxf(m_run, m2);
-      const float ca = (mm == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m_run - mm);
-      const float cb2 = (mm == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m2 - mm);
-      l_run = l_run * ca + l2 * cb2;
-      m_run = mm;
+      for (int v = 0; v < 3; ++v) {
+        const int slot = u * 3 + v;
+        const float m2 = s_m[slot * 16 + lc], l2 = s_l[slot * 16 + lc];
+        const float mm = fmaxf(m, m2);
+        const float ca = (mm == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - mm);
+        const float cb2 = (mm == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m2 - mm);
+        ls = ls * ca + l2 * cb2;
+        m = mm;
 #pragma unroll
-      for (int dt = 0; dt < ND; ++dt) {
-        const f32x4 x = *(const f32x4*)(s_of + u * 16 * OS + lc * OS + 16 * dt + 4 * lg);
-        o[dt] = o[dt] * ca + x * cb2;
+        for (int dt = 0; dt < ND; ++dt) {
+          const f32x4 x = *(const f32x4*)(s_of + slot * 16 * OS + lc * OS + 16 * dt + 4 * lg);
+          o[u][dt] = o[u][dt] * ca + x * cb2;
+        }
       }
-    }
-    // ---- the tile's columns: the output (one workgroup) or the workgroup's partial
-    if (c < NQ) {
-      const int row = wi.row0 + c / a.G, head = kvh * a.G + c % a.G;
-      const size_t col = ((size_t)kvh * a.max_wg + ((wi.info >> 8) & 0xffff)) * ncols + (size_t)wi.row0 * a.G + c;
-      if (wi.info & (1 << 24)) {
-        const float inv = 1.f / l_run;
-        if (a.ofrag != nullptr) {
+      // ---- the tile's columns: the output (one workgroup) or the workgroup's partial
+      const int cu = c + 16 * u;
+      if (cu < NQ) {
+        const int row = wi.row0 + cu / a.G, head = kvh * a.G + cu % a.G;
+        const size_t col = ((size_t)kvh * a.max_wg + ((wi.info >> 8) & 0xffff)) * ncols + (size_t)wi.row0 * a.G + cu;
+        if (wi.info & (1 << 24)) {
+          const float inv = 1.f / ls;
+          if (a.ofrag != nullptr) {
 #pragma unroll
-          for (int dt = 0; dt < ND; ++dt) st_frag4(a.ofrag, row, head * HD + 16 * dt + 4 * lg, a.hq * HD >> 5, o[dt] * inv);
+            for (int dt = 0; dt < ND; ++dt)
+              st_frag4(a.ofrag, row, head * HD + 16 * dt + 4 * lg, a.hq * HD >> 5, o[u][dt] * inv);
+          } else {
+            float* out = a.o + ((size_t)row * a.hq + head) * HD;
+#pragma unroll
+            for (int dt = 0; dt < ND; ++dt) *(f32x4*)(out + 16 * dt + 4 * lg) = o[u][dt] * inv;
+          }
+        } else if (fuse_n) {  // device-scope stores: another XCD's workgroup may merge them
+#pragma unroll
+          for (int dt = 0; dt < ND; ++dt) st_dev16(rpart, (uint32_t)((col * HD + 16 * dt + 4 * lg) * 4), o[u][dt]);
+          if (lg == 0) st_dev8(rml, (uint32_t)(col * 8), m, ls);
         } else {
-          float* out = a.o + ((size_t)row * a.hq + head) * HD;
 #pragma unroll
-          for (int dt = 0; dt < ND; ++dt) *(f32x4*)(out + 16 * dt + 4 * lg) = o[dt] * inv;
-        }
-      } else if (fuse_n) {  // device-scope stores: another XCD's workgroup may merge them
-#pragma unroll
-        for (int dt = 0; dt < ND; ++dt) st_dev16(rpart, (uint32_t)((col * HD + 16 * dt + 4 * lg) * 4), o[dt]);
-        if (lg == 0) st_dev8(rml, (uint32_t)(col * 8), m_run, l_run);
-      } else {
-#pragma unroll
-        for (int dt = 0; dt < ND; ++dt) *(f32x4*)(a.part + col * HD + 16 * dt + 4 * lg) = o[dt];
-        if (lg == 0) {
-          a.ml[col * 2 + 0] = m_run;
-          a.ml[col * 2 + 1] = l_run;
+          for (int dt = 0; dt < ND; ++dt) *(f32x4*)(a.part + col * HD + 16 * dt + 4 * lg) = o[u][dt];
+          if (lg == 0) {
+            a.ml[col * 2 + 0] = m;
+            a.ml[col * 2 + 1] = ls;
+          }
         }
       }
-    }
+    });
   }
   if (fuse_n == 0) return;
 
   // ---- fused group: count this workgroup's arrival once its partial is stored; the last of
   // the group's fuse_n workgroups combines every split (slots 0 .. fuse_n-1, fixed order):
   // o = sum_s O_s 2^(m_s - M) / sum_s l_s 2^(m_s - M), then re-arms the counter.
-  __shared__ unsigned s_tk;
+  unsigned& s_tk = *(unsigned*)(s_l + NT * 48);
   unsigned* cnt = a.cnt + ((size_t)kvh * kMaxGroups + (wi.nrows >> 16)) * kAttnCntStride;
   if (w == 0) {
     wait_mem();
@@ -603,7 +644,12 @@ hipError_t launch_attn_merge(const AttnArgs& a, int M, int hd, int nslots, hipSt
 template <class KT, int HD>
 static hipError_t launch_hd(const AttnArgs& a, dim3 grid, hipStream_t s) {
   const dim3 block(64 * kAttnWaves);
-  return a.long_runs ? launch_k(k_attn<KT, HD, true>, grid, block, s, a) : launch_k(k_attn<KT, HD, false>, grid, block, s, a);
+  if (a.tiles == 2) {
+    if constexpr (sizeof(KT) < 4) return launch_k(k_attn<KT, HD, true, 2>, grid, block, s, a);
+    return hipErrorInvalidValue;  // (fp32 pools: one tile per item)
+  }
+  return a.long_runs ? launch_k(k_attn<KT, HD, true, 1>, grid, block, s, a)
+                     : launch_k(k_attn<KT, HD, false, 1>, grid, block, s, a);
 }
 
 hipError_t launch_attn(int dtype, int hd, const AttnArgs& a, dim3 grid, hipStream_t s) {

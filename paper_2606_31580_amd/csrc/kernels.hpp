@@ -46,7 +46,7 @@ struct AttnItem {
   int seq, row0, nrows;  // the group's block table and rows (bits 0-7; fused: see above)
   int p0, pend, pps;
   int maxpos;            // last position any row of the group sees
-  int info;              // tile (bits 0-7) | partial slot (bits 8-23) | direct output (bit 24)
+  int info;              // tile, or pair of tiles (bits 0-7) | partial slot (bits 8-23) | direct output (bit 24)
 };
 constexpr int kAttnCntStride = 16;  // arrival counters 64 bytes apart: [kv head][group]
 // LM-head output row: activation row, destination (sel, off) for token / prob / logits.
@@ -175,6 +175,7 @@ struct AttnArgs {
   float* ml;    // [hkv][max_wg][max_rows*G][2]
   int max_wg;   // partial slots per (kv head, column): kAttnMaxWG, fewer when a wide prefill's rows share the buffer
   int long_runs;  // some item's waves walk more than two pages
+  int tiles;      // query tiles per item (1; 2 where a group has more than 16 columns)
   char* ofrag;  // the output as fragments for the O-projection (null: fp32 rows in o)
   uint32_t part_bytes, ml_bytes;
   unsigned* cnt;  // fused groups' arrival counters [hkv][kMaxGroups] x kAttnCntStride; zero between kernels

@@ -111,12 +111,12 @@ struct FwdKey {
   int M, n_out, agx, mslots, merge;  // agx: attention work items (grid width)
   int mo;                              // the split merge runs in the O-projection's launch
   int frag;                            // the projections run on the fragment path (fixed by M)
-  int long_runs;                       // attention runs of more than two pages
+  int long_runs, attn_tiles;           // attention: runs of more than two pages; query tiles per item
   uint64_t kv_id;
   // same launches apart from the attention grid width
   bool same_shape(const FwdKey& o) const {
     return M == o.M && n_out == o.n_out && mslots == o.mslots && merge == o.merge && mo == o.mo &&
-           long_runs == o.long_runs && kv_id == o.kv_id;
+           long_runs == o.long_runs && attn_tiles == o.attn_tiles && kv_id == o.kv_id;
   }
 };
 
@@ -1016,7 +1016,7 @@ static laser_status flush_pending(laser_kv* kv, laser_model* m, hipStream_t s, P
 // of all of them (each shared page is read once for every row), and each run keeps a group
 // of its own for its later pages.  A row's partials from the two are merged like any split.
 // The rows are reordered so that a family's runs are contiguous (outputs follow their rows).
-static void plan_groups(const laser_model* m, const laser_kv* kv, Plan& p, int slot_cap) {
+static int plan_groups(const laser_model* m, const laser_kv* kv, Plan& p, int slot_cap) {
   const laser_model_desc& d = m->desc;
   const int G = d.n_q_heads / d.n_kv_heads;
   struct Run {
@@ -1117,7 +1117,21 @@ static void plan_groups(const laser_model* m, const laser_kv* kv, Plan& p, int s
   // go to the 8 XCDs in turn: they share one XCD's L2).  Partial slots of a row: its
   // shared-pages group's splits, then its own group's; own groups next to a shared one get at
   // most kOwnSlots splits.
-  auto ntiles = [&](const GroupDesc& g) { return ceil_div(g.nrows * G, 16); };
+  int tiles = 1;  // query tiles per item
+  auto ntiles = [&](const GroupDesc& g) { return ceil_div(g.nrows * G, 16 * tiles); };
+  if (m->kv_es < 4) {
+    // Two tiles per item where a group has several and items of two still fill the chip: each page
+    // is then loaded once for both.
+    bool several = false;
+    long long wgs = 0;
+    tiles = 2;
+    for (int i = 0; i < p.n_groups; ++i) {
+      const GroupDesc& g = p.groups[i];
+      several |= g.nrows * G > 16;
+      wgs += (long long)ceil_div(g.npages - g.pbeg, kAttnWaves * kMaxPagesPerWave) * ntiles(g) * d.n_kv_heads;
+    }
+    if (!several || wgs < 2 * m->cus) tiles = 1;
+  }
   long long units = 0;
   for (int i = 0; i < p.n_groups; ++i)
     units += (long long)(p.groups[i].npages - p.groups[i].pbeg) * d.n_kv_heads * ntiles(p.groups[i]);
@@ -1136,7 +1150,7 @@ static void plan_groups(const laser_model* m, const laser_kv* kv, Plan& p, int s
     // round), and a last round that is nearly empty costs most (runs of 16 pages: 1.4 rounds, the
     // step 840 against 800 us).
     const int pos_bytes = d.head_dim * m->kv_es;  // a wave's ring takes 64 of these, of 160 KB per CU
-    const int resident = m->cus * (pos_bytes >= 512 ? 1 : pos_bytes >= 256 ? 2 : 3);
+    const int resident = m->cus * (pos_bytes >= 512 ? 1 : pos_bytes >= 256 || tiles == 2 ? 2 : 3);
     auto workgroups = [&](int b) {
       long long n = 0;
       for (int i = 0; i < p.n_groups; ++i)
@@ -1212,6 +1226,7 @@ static void plan_groups(const laser_model* m, const laser_kv* kv, Plan& p, int s
       for (int t = 0; t < T; ++t)
         for (int j = 0; j < 8; ++j) push(c + j < g.nwg ? &g : nullptr, c + j, t);
   }
+  return tiles;
 }
 
 // Pads the work items with empty ones up to n (the grid width of the launch).
@@ -1259,10 +1274,11 @@ static laser_status launch_forward(laser_model* m, laser_kv* kv, const FwdKey& k
 static laser_status run_forward(laser_model* m, laser_kv* kv, Plan& p, const PlanIO& io, hipStream_t s,
                                 bool allow_graph = true, const Scratch* sc_in = nullptr) {
   const Scratch sc = sc_in ? *sc_in : workspace_scratch(m, p.M);
-  plan_groups(m, kv, p, sc.max_wg);
+  const int attn_tiles = plan_groups(m, kv, p, sc.max_wg);
   p.io = io;
   FwdKey key{};
   key.M = p.M;
+  key.attn_tiles = attn_tiles;
   key.n_out = p.n_out;
   int max_slots = 1;
   bool merge = false;
@@ -1517,6 +1533,7 @@ static laser_status launch_forward(laser_model* m, laser_kv* kv, const FwdKey& k
   aa.max_rows = sc.rows;
   aa.max_wg = sc.max_wg;
   aa.long_runs = key.long_runs;
+  aa.tiles = key.attn_tiles;
   aa.ofrag = key.frag ? m->wsp<char>(L.o) : nullptr;
   aa.scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)hd));
   aa.part = sc.attn_part;
