@@ -268,10 +268,27 @@ hipError_t launch_lm_reduce(const Plan* plan, const LmPart* part, int n_groups, 
 hipError_t launch_embed(int dtype, const Plan* plan, int M, const void* embed, int d, int vocab, float* h, int* bt,
                         int max_pps, hipStream_t s);
 hipError_t launch_apply_bt(const Plan* plan, int* bt, int max_pps, hipStream_t s);
-// Copies a staged plan (pinned host slot) to the device plan slot; the kernel's address, so a
-// captured forward's copy can be pointed at the next slot before each replay.
+// Copies a staged plan (pinned host slot) to the device plan slot.
 hipError_t launch_plan_fetch(const Plan* src, Plan* dst, hipStream_t s);
-const void* plan_fetch_kernel();
+// The same, with the embedding gather of up to kMaxRows rows in one launch (gain: with the first
+// norm on the fragment path); the kernel's address and its arguments in order, so that a captured
+// forward's launch can be pointed at the next slot before each replay.
+struct FetchEmbedArgs {
+  const Plan* src;
+  Plan* dst;
+  const void* embed;
+  int d, vocab;
+  float* h;
+  int* bt;
+  int max_pps;
+  const void* gain;
+  float eps;
+  char* xfrag;
+  float* row_scale;
+};
+hipError_t launch_fetch_embed(int dtype, const FetchEmbedArgs& f, int M, hipStream_t s);
+const void* fetch_embed_kernel(int dtype);
+void fetch_embed_params(FetchEmbedArgs& f, void* (&p)[12]);
 // kv_es: bytes per KV element (1 fp8, 2 bf16, 4 fp32); the copy moves raw elements.
 hipError_t launch_kv_copy(int kv_es, int to_pool, void* kpool, void* vpool, const int* bt, int max_pps,
                           int num_pages, int n_layers, int hkv, int hd, int seq, int len, void* k_lin,

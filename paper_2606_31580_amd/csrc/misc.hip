@@ -292,7 +292,7 @@ hipError_t launch_lm_reduce(const Plan* plan, const LmPart* part, int n_groups, 
 // of loads (16 KB), then the rest of the items and the block-table updates, whose counts the
 // head gives.  One workgroup; the next kernel of the forward sees the copy after the boundary.
 constexpr int kFetchThreads = 1024;
-__global__ __launch_bounds__(kFetchThreads) void k_plan_fetch(const Plan* src, Plan* dst) {
+__device__ __forceinline__ void plan_fetch(const Plan* src, Plan* dst) {
   const char* s = (const char*)src;
   char* d = (char*)dst;
   const int t = threadIdx.x;
@@ -327,11 +327,97 @@ __global__ __launch_bounds__(kFetchThreads) void k_plan_fetch(const Plan* src, P
     *(u32x4*)(d + o) = ld_global<u32x4>(s + o);
 }
 
+__global__ __launch_bounds__(kFetchThreads) void k_plan_fetch(const Plan* src, Plan* dst) { plan_fetch(src, dst); }
+
+// The first kernel of a forward of up to kMaxRows rows: block 0 copies the plan as above and applies
+// its block-table updates; block 1 + m gathers row m's embedding, its row descriptor and token
+// pointers read from the staging slot like the plan itself (two reads over the bus in flight
+// together), so the gather does not wait for the copy and a kernel boundary (copy 4.6 us, boundary,
+// gather 4.8 us as two kernels).  With a gain (fragment path), the row's gain times h goes out as
+// fragments and its 1 / rms too, as k_resid_norm would write them.
+template <class WT>
+__global__ __launch_bounds__(kFetchThreads) void k_fetch_embed(const Plan* src, Plan* dst, const void* embed, int d,
+                                                                int vocab, float* h, int* bt, int max_pps,
+                                                                const uint16_t* gain, float eps, char* xfrag,
+                                                                float* row_scale) {
+  const int tid = threadIdx.x;
+  if (blockIdx.x == 0) {
+    const int n_bt = min(max(ld_global<int>(&src->n_bt), 0), kMaxBt);  // in flight with the copy
+    plan_fetch(src, dst);
+    for (int i = tid; i < n_bt; i += kFetchThreads) {
+      const int* u = &src->bt[i].seq;
+      bt[(size_t)ld_global<int>(u) * max_pps + ld_global<int>(u + 1)] = ld_global<int>(u + 2);
+    }
+    return;
+  }
+  __shared__ int s_tok;
+  __shared__ float s_sq[kFetchThreads / 64];
+  const int m = blockIdx.x - 1;
+  if (tid < 64) {  // wave 0: the descriptor and both token pointers, then the token
+    const u32x2 rd = ld_global<u32x2>(&src->rows[m].tok_sel);  // tok_sel, tok_off
+    const uint64_t p0 = ld_global<uint64_t>(&src->io.tok_src[0]), p1 = ld_global<uint64_t>(&src->io.tok_src[1]);
+    int tok = ld_global<int>((const int*)(rd[0] ? p1 : p0) + (int)rd[1]);
+    if (tok < 0 || tok >= vocab) tok = 0;  // ids outside the vocabulary never index past the table
+    if (tid == 0) s_tok = tok;
+  }
+  __syncthreads();
+  const size_t row = (size_t)s_tok * d;
+  float sq = 0.f;
+  for (int c = 8 * tid; c < d; c += 8 * kFetchThreads) {
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = ldw<WT>(embed, row + c + e);
+    float4* hp = (float4*)(h + (size_t)m * d + c);
+    hp[0] = make_float4(v[0], v[1], v[2], v[3]);
+    hp[1] = make_float4(v[4], v[5], v[6], v[7]);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sq = fmaf(v[e], v[e], sq);
+  }
+  if (gain == nullptr) return;
+  sq = wave_sum(sq);
+  if ((tid & 63) == 0) s_sq[tid >> 6] = sq;
+  __syncthreads();
+  if (tid == 0) {
+    float tot = 0.f;
+    for (int w = 0; w < kFetchThreads / 64; ++w) tot += s_sq[w];
+    row_scale[m] = rsqrtf(tot / (float)d + eps);
+  }
+  for (int c = 8 * tid; c < d; c += 8 * kFetchThreads) {
+    float y[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) y[e] = ldw<WT>(embed, row + c + e) * bf2f(ld_global<uint16_t>(gain + c + e));
+    u32x4 hi, lo;
+    split8(y, hi, lo);
+    const size_t o = frag_off(m, c, d >> 5);
+    *(u32x4*)(xfrag + o) = hi;
+    *(u32x4*)(xfrag + (o ^ 64)) = lo;
+  }
+}
+
+hipError_t launch_fetch_embed(int dtype, const FetchEmbedArgs& f, int M, hipStream_t s) {
+  if (M < 1 || M > kMaxRows || f.d % 8 != 0 || (f.gain != nullptr && (dtype != 1 || f.d % 32 != 0))) return hipErrorInvalidValue;
+  const dim3 grid(M + 1), block(kFetchThreads);
+  const uint16_t* gain = (const uint16_t*)f.gain;
+  if (dtype == 1)
+    return launch_k(k_fetch_embed<bf16_t>, grid, block, s, f.src, f.dst, f.embed, f.d, f.vocab, f.h, f.bt, f.max_pps, gain,
+                    f.eps, f.xfrag, f.row_scale);
+  return launch_k(k_fetch_embed<float>, grid, block, s, f.src, f.dst, f.embed, f.d, f.vocab, f.h, f.bt, f.max_pps, gain,
+                  f.eps, f.xfrag, f.row_scale);
+}
+
+// The kernel's arguments in order, for pointing a captured launch at the next staging slot.
+void fetch_embed_params(FetchEmbedArgs& f, void* (&p)[12]) {
+  void* a[12] = {&f.src, &f.dst, &f.embed, &f.d, &f.vocab, &f.h, &f.bt, &f.max_pps, &f.gain, &f.eps, &f.xfrag, &f.row_scale};
+  for (int i = 0; i < 12; ++i) p[i] = a[i];
+}
+
 hipError_t launch_plan_fetch(const Plan* src, Plan* dst, hipStream_t s) {
   return launch_k(k_plan_fetch, dim3(1), dim3(kFetchThreads), s, src, dst);
 }
 
-const void* plan_fetch_kernel() { return reinterpret_cast<const void*>(&k_plan_fetch); }
+const void* fetch_embed_kernel(int dtype) {
+  return dtype == 1 ? (const void*)&k_fetch_embed<bf16_t> : (const void*)&k_fetch_embed<float>;
+}
 
 hipError_t launch_apply_bt(const Plan* plan, int* bt, int max_pps, hipStream_t s) {
   hipLaunchKernelGGL(k_apply_bt, dim3(1), dim3(256), 0, s, plan, bt, max_pps);

@@ -74,9 +74,8 @@ constexpr int kMaxT = 16;   // trial tokens per probe
 #define LASER_ATTN_TARGET_WAVES 2048
 #endif
 constexpr int kTargetAttnWaves = LASER_ATTN_TARGET_WAVES;  // attention waves a forward aims for
-// A wave walks its pages with two in flight, so a long run is a chain of memory round trips:
-// past the wave target, more waves of at most 4 pages beat longer runs (batch 8 at 68k
-// positions: attention + merge 78 -> 61 us per layer; 2 pages: 68 us, 8 pages: 73 us).
+// Pages per wave from which the planner starts to lengthen runs until every workgroup is resident
+// (plan_groups).
 #ifndef LASER_ATTN_MAX_PPS
 #define LASER_ATTN_MAX_PPS 4
 #endif
@@ -437,7 +436,8 @@ static FragShape frag_shape(int epi, int n_groups, int M, int K, int cus) {
   return best;
 }
 
-// QKV over K slices (launch_qkv_slices): forwards of kQSliceMinRows to 64 rows, bf16 weights
+// QKV over K slices (launch_qkv_slices): forwards of kQSliceMinRows to 64 rows, bf16 weights that the
+// fragment path does not take
 // (tile order when the copy is there).  Each workgroup stages a 512-column slice of K of every
 // activation row in LDS and runs 16 row groups over it.  Measured against the K-split kernel,
 // which reads all of K of every activation row for each of its one or two row groups: QKV of
@@ -1268,6 +1268,16 @@ static Scratch workspace_scratch(const laser_model* m, int M) {
 static laser_status launch_forward(laser_model* m, laser_kv* kv, const FwdKey& key, hipStream_t s, const Scratch& sc,
                                    const Plan* hp);
 
+// Arguments of a forward's first launch (up to kMaxRows rows).
+static FetchEmbedArgs fetch_embed_args(const laser_model* m, const laser_kv* kv, const FwdKey& key, const Scratch& sc,
+                                       const Plan* hp) {
+  const laser_model_desc& d = m->desc;
+  const Layout& L = m->lay;
+  return FetchEmbedArgs{hp, m->wsp<Plan>(L.plans), m->embed, d.d_model, d.vocab, m->wsp<float>(L.h), kv->bt,
+                        kv->pool.max_pages_per_seq(), key.frag ? m->layers[0].attn_norm : nullptr, d.rms_eps, sc.xfrag,
+                        m->wsp<float>(L.row_scale)};
+}
+
 // Runs one forward: plans the attention splits, stages the plan, then launches the
 // forward's kernels (replaying a captured graph of them when graphs are on and no kernel
 // class is being timed).
@@ -1354,14 +1364,14 @@ static laser_status run_forward(laser_model* m, laser_kv* kv, Plan& p, const Pla
       return st;
     }
     if (ec != hipSuccess) return laser_fail(LASER_ERR_HIP, "graph capture: %s", hipGetErrorString(ec));
-    // the plan copy is the one root: every other kernel follows it in stream order
+    // the launch with the plan copy is the one root: every other kernel follows it in stream order
     hipGraphNode_t fetch = nullptr;
     size_t n_roots = 1;
     hipKernelNodeParams fp{};
     hipGraphNodeType ty{};
     if (hipGraphGetRootNodes(graph, &fetch, &n_roots) != hipSuccess || n_roots != 1 ||
         hipGraphNodeGetType(fetch, &ty) != hipSuccess || ty != hipGraphNodeTypeKernel ||
-        hipGraphKernelNodeGetParams(fetch, &fp) != hipSuccess || fp.func != plan_fetch_kernel()) {
+        hipGraphKernelNodeGetParams(fetch, &fp) != hipSuccess || fp.func != fetch_embed_kernel(m->desc.dtype == LASER_DTYPE_BF16 ? 1 : 0)) {
       (void)hipGraphDestroy(graph);
       return laser_fail(LASER_ERR_HIP, "graph capture: the plan copy is not the forward's only root");
     }
@@ -1390,8 +1400,9 @@ static laser_status run_forward(laser_model* m, laser_kv* kv, Plan& p, const Pla
   }
   ge->last_use = ++m->graph_clock;
   {  // the replay's plan copy reads this call's staging slot
-    Plan* dp = m->wsp<Plan>(m->lay.plans);
-    void* args[2] = {(void*)&hp, (void*)&dp};
+    FetchEmbedArgs fe = fetch_embed_args(m, kv, key, sc, hp);
+    void* args[12];
+    fetch_embed_params(fe, args);
     hipKernelNodeParams kp = ge->fetch_params;
     kp.kernelParams = args;
     kp.extra = nullptr;
@@ -1419,7 +1430,11 @@ static laser_status launch_forward(laser_model* m, laser_kv* kv, const FwdKey& k
   laser_status st = LASER_OK;
   float* h = m->wsp<float>(L.h);
   float* row_scale = m->wsp<float>(L.row_scale);  // (fragment path)
-  HIP_TRY(timed(m, LASER_K_EMBED, s, [&] {  // the plan copy (from the staging slot hp), then the embedding gather
+  if (key.M <= kMaxRows) {  // the plan copy (from the staging slot hp) and the embedding gather in one launch
+    const FetchEmbedArgs fe = fetch_embed_args(m, kv, key, sc, hp);
+    HIP_TRY(timed(m, LASER_K_EMBED, s, [&] { return launch_fetch_embed(dt, fe, key.M, s); }));
+  } else {
+  HIP_TRY(timed(m, LASER_K_EMBED, s, [&] {
     const hipError_t e = launch_plan_fetch(hp, m->wsp<Plan>(L.plans), s);
     return e == hipSuccess ? launch_embed(dt, dp, key.M, m->embed, d.d_model, d.vocab, h, kv->bt, max_pps, s) : e;
   }));
@@ -1427,6 +1442,7 @@ static laser_status launch_forward(laser_model* m, laser_kv* kv, const FwdKey& k
     HIP_TRY(timed(m, LASER_K_OTHER, s, [&] {
       return launch_resid_norm(h, nullptr, 0, key.M, d.d_model, m->layers[0].attn_norm, d.rms_eps, sc.xfrag, row_scale, s);
     }));
+  }
 
   GemmArgs base{};
   base.plan = dp;
