@@ -68,7 +68,7 @@ struct PlanIO {
 
 // Everything the kernels of one forward need that changes per call; uploaded once (the used
 // part of each array).
-struct alignas(16) Plan {  // (16-byte aligned arrays: k_plan_fetch copies 16-byte chunks)
+struct alignas(16) Plan {  // (16-byte aligned arrays: the plan copy kernels move 16-byte chunks)
   int M, n_groups, n_out, n_bt, n_items;
   // split merge carried by the O-projection's launch: the value every layer's merge counter
   // reaches once this forward's merge workgroups of that layer have stored their outputs

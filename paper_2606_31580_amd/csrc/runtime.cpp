@@ -948,9 +948,10 @@ static hipError_t timed(laser_model* m, int cls, hipStream_t s, F&& f) {
 
 // Copies the used part of a plan into the next pinned staging slot, once the forward that
 // last used the slot has finished (slots are taken in turn; the event recorded after the last
-// slot of each block of kRingEventEvery is awaited before the block's first slot is reused).  The forward's first kernel (k_plan_fetch) copies it on to
-// the device plan slot, so a replayed forward is one graph launch with no copy command before
-// it (a host-to-device copy between graph launches cost about 20 us of idle time per step).
+// slot of each block of kRingEventEvery is awaited before the block's first slot is reused).
+// The forward's first kernel (k_fetch_embed, or k_plan_fetch where the gather is a launch of its
+// own) copies it on to the device plan slot, so a replayed forward is one graph launch with no
+// copy command before it (a host-to-device copy between graph launches cost about 20 us of idle time per step).
 // staged_done marks the slot in use until the work now on the stream has finished.
 static laser_status stage_plan(laser_model* m, const Plan& p, const Plan** hp_out, int* slot_out) {
   const int slot = m->ring_pos;
