@@ -267,7 +267,8 @@ hipError_t launch_attn_merge(const AttnArgs& a, int M, int hd, int nslots, hipSt
 hipError_t launch_lm_reduce(const Plan* plan, const LmPart* part, int n_groups, int n_out, hipStream_t s);
 hipError_t launch_embed(int dtype, const Plan* plan, int M, const void* embed, int d, int vocab, float* h, int* bt,
                         int max_pps, hipStream_t s);
-hipError_t launch_apply_bt(const Plan* plan, int* bt, int max_pps, hipStream_t s);
+// Writes a staged plan's block-table updates (pinned host slot) to the block table.
+hipError_t launch_bt_upload(const Plan* src, int* bt, int max_pps, hipStream_t s);
 // Copies a staged plan (pinned host slot) to the device plan slot.
 hipError_t launch_plan_fetch(const Plan* src, Plan* dst, hipStream_t s);
 // The same, with the embedding gather of up to kMaxRows rows in one launch (gain: with the first

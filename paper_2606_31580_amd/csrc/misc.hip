@@ -96,8 +96,6 @@ __global__ __launch_bounds__(kLmThreads) void k_lm_reduce(const Plan* plan, cons
   }
 }
 
-__global__ void k_apply_bt(const Plan* plan, int* bt, int max_pps) { apply_bt_updates(plan, bt, max_pps); }
-
 // The same copy in 16-byte pieces, for dense arrays that are 16-byte aligned.  A thread moves 4
 // positions x 8 dims of K and of V: four 8-element loads each (consecutive threads read
 // consecutive bytes of a position), which in a page block are 32 consecutive elements: K chunks of
@@ -329,6 +327,20 @@ __device__ __forceinline__ void plan_fetch(const Plan* src, Plan* dst) {
 
 __global__ __launch_bounds__(kFetchThreads) void k_plan_fetch(const Plan* src, Plan* dst) { plan_fetch(src, dst); }
 
+// Block-table updates outside a forward (before an import, export, fork or the next forward), from
+// the staging slot straight into the table: each thread reads the count and its own update in one
+// round over the bus (entries past the count are stale but inside the slot, and unused).  Bounded by
+// that round trip; as a plan copy and a second kernel on the copy it was three dependent memory
+// rounds and a kernel boundary (an import of 6,001 positions at the 7B shape's heads, 8 layers: the
+// call 63.2 us then, 60.2 us so).
+__global__ __launch_bounds__(kMaxBt) void k_bt_upload(const Plan* src, int* bt, int max_pps) {
+  const int i = threadIdx.x;
+  const int n = ld_global<int>(&src->n_bt);
+  const int* u = &src->bt[i].seq;
+  const int seq = ld_global<int>(u), idx = ld_global<int>(u + 1), page = ld_global<int>(u + 2);
+  if (i < n) bt[(size_t)seq * max_pps + idx] = page;
+}
+
 // The first kernel of a forward of up to kMaxRows rows: block 0 copies the plan as above and applies
 // its block-table updates; block 1 + m gathers row m's embedding, its row descriptor and token
 // pointers read from the staging slot like the plan itself (two reads over the bus in flight
@@ -419,9 +431,8 @@ const void* fetch_embed_kernel(int dtype) {
   return dtype == 1 ? (const void*)&k_fetch_embed<bf16_t> : (const void*)&k_fetch_embed<float>;
 }
 
-hipError_t launch_apply_bt(const Plan* plan, int* bt, int max_pps, hipStream_t s) {
-  hipLaunchKernelGGL(k_apply_bt, dim3(1), dim3(256), 0, s, plan, bt, max_pps);
-  return hipGetLastError();
+hipError_t launch_bt_upload(const Plan* src, int* bt, int max_pps, hipStream_t s) {
+  return launch_k(k_bt_upload, dim3(1), dim3(kMaxBt), s, src, bt, max_pps);
 }
 
 hipError_t launch_kv_copy(int kv_es, int to_pool, void* kpool, void* vpool, const int* bt, int max_pps,

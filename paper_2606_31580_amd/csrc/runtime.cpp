@@ -863,7 +863,13 @@ extern "C" laser_status laser_kv_add_seq(laser_kv* kv, int seq_id, int length) {
 
 extern "C" laser_status laser_kv_free_seq(laser_kv* kv, int seq_id) {
   if (!kv_of(kv)) return laser_fail(LASER_ERR_STATE, "invalid or destroyed kv");
-  return (laser_status)kv->pool.free_seq(seq_id);
+  const laser_status st = (laser_status)kv->pool.free_seq(seq_id);
+  // table rows of the slot that have not been sent are void: the slot's next sequence writes the
+  // same entries, and updates sent together are written in no order
+  if (st == LASER_OK && !kv->pending.empty())
+    kv->pending.erase(std::remove_if(kv->pending.begin(), kv->pending.end(), [&](const PageUpdate& u) { return u.seq == seq_id; }),
+                      kv->pending.end());
+  return st;
 }
 
 extern "C" laser_status laser_kv_seq_len(const laser_kv* kv, int seq_id, int* len_out) {
@@ -1000,10 +1006,8 @@ static laser_status flush_pending(laser_kv* kv, laser_model* m, hipStream_t s, P
     laser_status st = stage_plan(m, *p, &hp, &slot);
     if (!buf) delete p;
     if (st != LASER_OK) return st;
-    Plan* dp = m->wsp<Plan>(m->lay.plans);  // stream order keeps forwards off each other's plan
     TimingScope scope(m);
-    HIP_TRY(launch_plan_fetch(hp, dp, s));
-    HIP_TRY(launch_apply_bt(dp, kv->bt, kv->pool.max_pages_per_seq(), s));
+    HIP_TRY(launch_bt_upload(hp, kv->bt, kv->pool.max_pages_per_seq(), s));
     st = staged_done(m, slot, s);
     if (st != LASER_OK) return st;
   }

@@ -71,3 +71,29 @@ def test_import_export_layout(hd, hkv, kind):
                 assert bool((b[:shift * es] == 0xEE).all()) and bool((b[shift * es + size * es:] == 0xEE).all())
             kv.destroy()
     model.destroy()
+
+
+@pytest.mark.parametrize("pages", [1, 63, 64, 65, 1023, 1024, 1025, 1600])
+def test_block_table_upload(pages):
+    """The device block table holds what page_table says: around a wave and around the 1,024 updates of
+    one upload, and for a slot that is freed and taken again before its first table went out."""
+    require_gpu()
+    shape = _shape(64, 1, "bf16")
+    w = {k: v.cuda() for k, v in synth.make_weights(shape).items()}
+    model = L.Model(shape, w, max_rows=4, max_positions=16 * pages, tiles=False)
+    kv = L.KVCache(model, 2 * pages + 4, 3, pages)
+    kv.block_table.fill_(-1)
+    kv.add_seq(2, 17 if pages > 1 else 3)
+    kv.add_seq(1, 16 * pages)
+    kv.free_seq(1)
+    kv.add_seq(0, 5)  # takes a page of the freed ones: the slot's next table is another one
+    kv.add_seq(1, 16 * pages - 7)
+    k = torch.zeros(3, 5, 1, 64, dtype=torch.bfloat16, device="cuda")
+    kv.export_kv(0, k, torch.zeros_like(k))
+    torch.cuda.synchronize()
+    bt = kv.block_table.cpu().view(3, pages)
+    for seq in range(3):
+        want = kv.page_table(seq)
+        assert bt[seq, :len(want)].tolist() == want, f"sequence {seq} of {pages} pages"
+    kv.destroy()
+    model.destroy()
