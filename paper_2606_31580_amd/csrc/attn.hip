@@ -519,7 +519,10 @@ __global__ __launch_bounds__(64 * kAttnWaves) void k_attn(AttnArgs a) {
       }
     }
     const int row = wi.row0 + cc / a.G, head = kvh * a.G + cc % a.G;
-    *(f32x4*)(a.o + ((size_t)row * a.hq + head) * HD + 4 * d4) = acc * (1.f / Ls);
+    if (a.ofrag != nullptr)
+      st_frag4(a.ofrag, row, head * HD + 4 * d4, a.hq * HD >> 5, acc * (1.f / Ls));
+    else
+      *(f32x4*)(a.o + ((size_t)row * a.hq + head) * HD + 4 * d4) = acc * (1.f / Ls);
   }
   if (tid == 0) __hip_atomic_store(cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }

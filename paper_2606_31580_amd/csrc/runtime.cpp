@@ -1180,7 +1180,7 @@ static int plan_groups(const laser_model* m, const laser_kv* kv, Plan& p, int sl
       GroupDesc& g = p.groups[i];
       const bool shares = row_prefix[g.row0] >= 0;
       const bool is_prefix = row_prefix[g.row0] == i;
-      const int max_wg = fusable(g) ? m->attn_fuse_max
+      const int max_wg = fusable(g) ? std::min(m->attn_fuse_max, slot_cap)
                                     : is_prefix ? kAttnMaxWG - kOwnSlots : (shares ? kOwnSlots : slot_cap);
       const int npg = g.npages - g.pbeg;
       g.pps = std::max(base, ceil_div(npg, max_wg * kAttnWaves));

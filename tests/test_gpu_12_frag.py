@@ -121,3 +121,37 @@ def test_probe_batches_and_mixed_steps():
         assert float((first[0] - first[1]).abs().max()) <= 2e-2
         np.testing.assert_allclose(out[0, True][2].cpu(), out[1, True][2].cpu(), rtol=4e-2)
     model.destroy()
+
+
+@pytest.mark.parametrize("shape,max_rows,rows", [(HD64, 20, 20), (HD128, 33, 33), (FP8, 17, 17), (HD64, 4, 65),
+                                                 (HD128, 16, 129), (FP8, 64, 65)],
+                         ids=lambda v: v.name if isinstance(v, ModelShape) else None)
+def test_merge_in_attention(shape, max_rows, rows):
+    # One-row attention groups that merge their splits inside the attention kernel, beside fragment
+    # projections: decode batches from 17 rows, and the single row past the last 64 of a wide prefill,
+    # whose splits have to fit that forward's partial slots.  Only the order of the fp32 merge differs.
+    require_gpu()
+    w = {k: v.cuda() for k, v in synth.make_weights(shape).items()}
+    model = L.Model(shape, w, max_rows=max_rows, max_positions=1024, poison=True)
+    decode = rows == max_rows
+    lens = [40 + 45 * (i % 20) for i in range(rows)] if decode else [850]
+    tok = synth.make_tokens(rows, shape.vocab, 29).cuda()
+    out = []
+    for fused in (False, True):
+        model.set_attn_merge(fused, 128)
+        kv = L.KVCache(model, 64 * len(lens), len(lens), 64, poison=True)
+        for i, n in enumerate(lens):
+            kv.add_seq(i, n)
+            kv.import_kv(i, *synth.make_prefill_kv(shape, n, 7 + i, device="cuda"))
+        if decode:
+            lg, p = torch.zeros(rows, shape.vocab, device="cuda"), torch.zeros(rows, device="cuda")
+            L.laser_decode_step(model, kv, list(range(rows)), tok, torch.zeros_like(tok), p, lg)
+        else:
+            lg = torch.zeros(shape.vocab, device="cuda")
+            L.laser_prefill(model, kv, 0, tok, lg)
+        torch.cuda.synchronize()
+        out.append(lg)
+        kv.destroy()
+    assert torch.isfinite(out[1]).all()
+    assert float((out[0] - out[1]).abs().max()) <= 2e-3
+    model.destroy()
