@@ -96,68 +96,48 @@ __global__ __launch_bounds__(kLmThreads) void k_lm_reduce(const Plan* plan, cons
   }
 }
 
-// The same copy in 16-byte pieces, for dense arrays that are 16-byte aligned.  A thread moves 4
-// positions x 8 dims of K and of V: four 8-element loads each (consecutive threads read
-// consecutive bytes of a position), which in a page block are 32 consecutive elements: K chunks of
-// 8 dims lie position by position, V as dims of 4 consecutive positions (transposed here in
-// registers).  The element-wise kernel below moves 2 bytes per load and store and stays for
-// other alignments and for the last 1-3 positions (6,001 positions of 8 layers x 4 heads x 128 in
-// bf16, 98 MB: 98 us element by element, 36 us so).
+// Copies one sequence between the paged pools and dense [n_layers][len][hkv][hd] arrays in pieces of
+// 8 elements (16 bytes of bf16; 8 of E4M3, 32 of fp32), for pools and dense arrays that are 16-byte
+// aligned.  A thread moves 4 positions x 8 dims of K, of V, or (BOTH) of each: four 8-element loads
+// (consecutive threads read consecutive bytes of a position), which in a page block are 32 consecutive
+// elements: K chunks of 8 dims lie position by position, V as dims of 4 consecutive positions
+// (transposed here in registers).  grid (4-position x 8-dim pieces of a layer / 256, layers, K and V).
+// Long transfers are bounded by memory (6,001 positions of 8 layers x 4 heads x 128 in bf16, 98 MB:
+// 98 us element by element, 36 us so), short ones by one thread's chain of page id, loads, stores.  So
+// the last 1-3 positions take the same path with their absent neighbours left out (element by element
+// they were a chain of up to 48 round trips: export of 63 positions, 4 layers x 4 heads x 128 in bf16,
+// the call 10.0 us against 6.6; 3,003 positions of 2 layers x 2 heads x 64 in fp32 10.5 against 6.7), and
+// the only division is by the head count, in 32 bits.
 template <int ES>  // bytes per element
 struct KvChunk {
   uint32_t w[2 * ES];  // 8 elements
 };
-template <int ES, bool TO_POOL>
+template <int ES, bool TO_POOL, bool BOTH>
 __global__ __launch_bounds__(256) void k_kv_copy16(void* kpool, void* vpool, const int* bt, int max_pps, int num_pages,
-                                                   int n_layers, int hkv, int hd, int seq, int len, void* k_lin,
-                                                   void* v_lin) {
+                                                   int hkv, int hd, int seq, int len, void* k_lin, void* v_lin) {
   using C = KvChunk<ES>;
-  const int nd8 = hd >> 3, npg = (len + 15) >> 4;
-  const size_t total = (size_t)n_layers * npg * 4 * hkv * nd8;
-  const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= total) return;
-  const int d8 = (int)(idx % nd8);
-  size_t r = idx / nd8;
-  const int kvh = (int)(r % hkv);
-  r /= hkv;
-  const int t4 = (int)(r & 3);
-  r >>= 2;
-  const int pg = (int)(r % npg), layer = (int)(r / npg);
-  const int pos = 16 * pg + 4 * t4, n = min(4, len - pos);
+  const unsigned idx = blockIdx.x * 256 + threadIdx.x;
+  const int layer = blockIdx.y;
+  const int ld8 = hd == 128 ? 4 : 3;  // log2 of a head's 8-dim pieces
+  const int d8 = idx & ((1u << ld8) - 1);
+  const unsigned r = idx >> ld8, pos4 = r / (unsigned)hkv;  // pos4: group of 4 positions
+  const int kvh = r - pos4 * hkv, pg = pos4 >> 2, t4 = pos4 & 3;
+  const int pos = 4 * (int)pos4, n = min(4, len - pos);
   if (n <= 0) return;
   const int page = bt[(size_t)seq * max_pps + pg];
   const size_t blk = (((size_t)layer * num_pages + page) * hkv + kvh) * (size_t)(16 * hd);
   const size_t lin = (((size_t)layer * len + pos) * hkv + kvh) * hd + 8 * d8, row = (size_t)hkv * hd;
-  const size_t ko = blk + k_block_off(4 * t4, 8 * d8), vo = blk + v_block_off(4 * t4, 8 * d8);
-  if (n < 4) {  // the sequence ends inside these 4 positions: element by element
-    using E = std::conditional_t<ES == 1, uint8_t, std::conditional_t<ES == 2, uint16_t, uint32_t>>;
-    for (int j = 0; j < n; ++j)
-      for (int e = 0; e < 8; ++e) {
-        E* kd = (E*)k_lin + lin + j * row + e;
-        E* vd = (E*)v_lin + lin + j * row + e;
-        E* kp = (E*)kpool + ko + 8 * j + e;
-        E* vp = (E*)vpool + vo + 4 * e + j;
-        if (TO_POOL) {
-          *kp = *kd;
-          *vp = *vd;
-        } else {
-          *kd = *kp;
-          *vd = *vp;
-        }
-      }
-    return;
-  }
   // a chunk is 8 ES bytes, loaded and stored as one or two vectors
   auto ld = [](const char* p) {
     C c;
     if constexpr (ES == 1) {
-      const u32x2 v = *(const u32x2*)p;
+      const u32x2 v = ld_global<u32x2>(p);
       c.w[0] = v[0];
       c.w[1] = v[1];
     } else {
 #pragma unroll
       for (int q = 0; q < ES / 2; ++q) {
-        const u32x4 v = *(const u32x4*)(p + 16 * q);
+        const u32x4 v = ld_global<u32x4>(p + 16 * q);
 #pragma unroll
         for (int i = 0; i < 4; ++i) c.w[4 * q + i] = v[i];
       }
@@ -182,35 +162,57 @@ __global__ __launch_bounds__(256) void k_kv_copy16(void* kpool, void* vpool, con
     if constexpr (ES == 2) c.w[e >> 1] |= v << (16 * (e & 1));
     if constexpr (ES == 1) c.w[e >> 2] |= v << (8 * (e & 3));
   };
-  char* kd = (char*)k_lin + lin * ES;
-  char* vd = (char*)v_lin + lin * ES;
-  char* kp = (char*)kpool + ko * ES;
-  char* vp = (char*)vpool + vo * ES;
-  C kc[4], vc[4], vt[4] = {};
+  // Positions past the length read the last one again (in a page: its own slots, which are there).
+  auto load = [&](bool is_v, C* c) {
+    const char* dense = (const char*)(is_v ? v_lin : k_lin) + lin * ES;
+    const char* pool = (const char*)(is_v ? vpool : kpool) + (blk + (is_v ? v_block_off(4 * t4, 8 * d8) : k_block_off(4 * t4, 8 * d8))) * ES;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    kc[j] = ld(TO_POOL ? kd + j * row * ES : kp + j * 8 * ES);
-    vc[j] = ld(TO_POOL ? vd + j * row * ES : vp + j * 8 * ES);
-  }
-  // dense (position j, dim e) <-> page block: element 4 e + j of the 32
+    for (int j = 0; j < 4; ++j) c[j] = ld(TO_POOL ? dense + min(j, n - 1) * row * ES : pool + j * 8 * ES);
+  };
+  auto store = [&](bool is_v, C* c) {
+    char* dense = (char*)(is_v ? v_lin : k_lin) + lin * ES;
+    char* pool = (char*)(is_v ? vpool : kpool) + (blk + (is_v ? v_block_off(4 * t4, 8 * d8) : k_block_off(4 * t4, 8 * d8))) * ES;
+    if (is_v) {  // dense (position j, dim e) <-> page block: element 4 e + j of the 32
+      if (TO_POOL && n < 4) {  // (slots past the length keep what they hold)
+        using E = std::conditional_t<ES == 1, uint8_t, std::conditional_t<ES == 2, uint16_t, uint32_t>>;
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < 3; ++j)
+          if (j < n)
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int x = 4 * e + j;
-      if constexpr (TO_POOL)
-        put(vt[x >> 3], x & 7, get(vc[j], e));
-      else
-        put(vt[j], e, get(vc[x >> 3], x & 7));
+            for (int e = 0; e < 8; ++e) ((E*)pool)[4 * e + j] = (E)get(c[j], e);
+        return;
+      }
+      C t[4] = {};
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int x = 4 * e + j;
+          if constexpr (TO_POOL)
+            put(t[x >> 3], x & 7, get(c[j], e));
+          else
+            put(t[j], e, get(c[x >> 3], x & 7));
+        }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) c[j] = t[j];
     }
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    st(TO_POOL ? kp + j * 8 * ES : kd + j * row * ES, kc[j]);
-    st(TO_POOL ? vp + j * 8 * ES : vd + j * row * ES, vt[j]);
+    for (int j = 0; j < 4; ++j)
+      if (j < n) st(TO_POOL ? pool + j * 8 * ES : dense + j * row * ES, c[j]);
+  };
+  C a[4], b[4];
+  if constexpr (BOTH) {
+    load(false, a);
+    load(true, b);
+    store(false, a);
+    store(true, b);
+  } else {
+    load(blockIdx.z, a);
+    store(blockIdx.z, a);
   }
 }
 
-// Copy one sequence between the paged pools and dense [n_layers][len][hkv][hd] arrays.
+// The same, one element per load and store, for any alignment.
 template <class WT>
 __global__ void k_kv_copy(int to_pool, void* kpool, void* vpool, const int* bt, int max_pps, int num_pages,
                           int n_layers, int hkv, int hd, int seq, int len, void* k_lin, void* v_lin) {
@@ -440,17 +442,24 @@ hipError_t launch_kv_copy(int kv_es, int to_pool, void* kpool, void* vpool, cons
                           void* v_lin, hipStream_t s) {
   const size_t total = (size_t)n_layers * len * hkv * hd;
   if (total == 0) return hipSuccess;
-  if ((((uintptr_t)k_lin | (uintptr_t)v_lin | (uintptr_t)kpool | (uintptr_t)vpool) & 15) == 0) {
-    const size_t threads = (size_t)n_layers * ((len + 15) / 16) * 4 * hkv * (hd / 8);
-    const dim3 grid((unsigned)((threads + 255) / 256));
+  if ((((uintptr_t)k_lin | (uintptr_t)v_lin | (uintptr_t)kpool | (uintptr_t)vpool) & 15) == 0 && n_layers <= 65535) {
+    // K and V on threads of their own but for imports past the 256 MB memory-side cache, whose writes
+    // go out better together (read and written: 197 MB, 8 layers x 4 heads x 6,001 positions, 38.6 us
+    // apart, 42.1 together; 574 MB, 5 layers x 8 heads x 14,001, 151 apart, 142 together; export 99 and 105)
+    const bool both = to_pool && 4 * total * kv_es > ((size_t)256 << 20);
+    const unsigned pieces = (unsigned)((len + 3) / 4) * hkv * (hd / 8);
+    const dim3 grid((pieces + 255) / 256, n_layers, both ? 1 : 2);
     auto go = [&](auto k) {
-      hipLaunchKernelGGL(k, grid, dim3(256), 0, s, kpool, vpool, bt, max_pps, num_pages, n_layers, hkv, hd, seq, len, k_lin,
-                         v_lin);
+      hipLaunchKernelGGL(k, grid, dim3(256), 0, s, kpool, vpool, bt, max_pps, num_pages, hkv, hd, seq, len, k_lin, v_lin);
       return hipGetLastError();
     };
-    if (kv_es == 1) return to_pool ? go(k_kv_copy16<1, true>) : go(k_kv_copy16<1, false>);
-    if (kv_es == 2) return to_pool ? go(k_kv_copy16<2, true>) : go(k_kv_copy16<2, false>);
-    return to_pool ? go(k_kv_copy16<4, true>) : go(k_kv_copy16<4, false>);
+    auto pick = [&](auto es) {
+      constexpr int ES = decltype(es)::value;
+      return !to_pool ? go(k_kv_copy16<ES, false, false>) : both ? go(k_kv_copy16<ES, true, true>) : go(k_kv_copy16<ES, true, false>);
+    };
+    if (kv_es == 1) return pick(std::integral_constant<int, 1>{});
+    if (kv_es == 2) return pick(std::integral_constant<int, 2>{});
+    return pick(std::integral_constant<int, 4>{});
   }
   size_t blocks = (total + 255) / 256;
   if (blocks > 65536) blocks = 65536;

@@ -73,6 +73,43 @@ def test_import_export_layout(hd, hkv, kind):
     model.destroy()
 
 
+def test_import_past_the_cache():
+    """An import of more than 256 MB read and written (K and V in one thread), its length ending inside a
+    group of 4 positions, against the layout written with torch; then exported again."""
+    require_gpu()
+    hkv, hd, n = 16, 128, 5603
+    shape = _shape(hd, hkv, "bf16")
+    w = {k: v.cuda() for k, v in synth.make_weights(shape).items()}
+    model = L.Model(shape, w, max_rows=4, max_positions=5616, tiles=False)
+    pages = (n + 15) // 16
+    kv = L.KVCache(model, pages + 1, 1, pages)
+    kv.k_pool.fill_(0xA5)
+    kv.v_pool.fill_(0xA5)
+    kv.add_seq(0, n)
+    g = torch.Generator(device="cuda").manual_seed(9)
+    dense = [torch.randint(-2 ** 15, 2 ** 15, (3, n, hkv, hd), generator=g, device="cuda", dtype=torch.int16) for _ in range(2)]
+    kv.import_kv(0, *dense)
+    torch.cuda.synchronize()
+    fill = int(np.array([0xA5A5], dtype=np.uint16).view(np.int16)[0])
+    for pool, d, is_k in ((kv.k_pool, dense[0], True), (kv.v_pool, dense[1], False)):
+        full = torch.full((3, pages * 16, hkv, hd), fill, dtype=torch.int16, device="cuda")
+        full[:, :n] = d
+        x = full.view(3, pages, 16, hkv, hd).transpose(2, 3)  # [layer][page][head][16][hd]
+        if is_k:  # chunks of 8 dims, position by position
+            x = x.reshape(3, pages, hkv, 16, hd // 8, 8).transpose(3, 4)
+        else:  # 16 dims x 4 positions
+            x = x.reshape(3, pages, hkv, 4, 4, hd // 16, 16).permute(0, 1, 2, 5, 3, 6, 4)
+        got = pool.view(torch.int16).view(3, pages + 1, -1)
+        assert torch.equal(got[:, :pages], x.reshape(3, pages, -1)), "K" if is_k else "V"
+        assert bool((got[:, pages] == fill).all())
+    back = [torch.zeros_like(d) for d in dense]
+    kv.export_kv(0, *back)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(back, dense))
+    kv.destroy()
+    model.destroy()
+
+
 @pytest.mark.parametrize("pages", [1, 63, 64, 65, 1023, 1024, 1025, 1600])
 def test_block_table_upload(pages):
     """The device block table holds what page_table says: around a wave and around the 1,024 updates of
