@@ -15,6 +15,7 @@
 #include <unordered_set>
 #include <vector>
 
+#include "attn_runs.hpp"
 #include "kernels.hpp"
 #include "laser.h"
 #include "laser_error.h"
@@ -74,14 +75,12 @@ constexpr int kMaxT = 16;   // trial tokens per probe
 #define LASER_ATTN_TARGET_WAVES 2048
 #endif
 constexpr int kTargetAttnWaves = LASER_ATTN_TARGET_WAVES;  // attention waves a forward aims for
-// Pages per wave from which the planner starts to lengthen runs until every workgroup is resident
-// (plan_groups).
+// Pages per wave from which the planner lengthens runs (run_pages).
 #ifndef LASER_ATTN_MAX_PPS
 #define LASER_ATTN_MAX_PPS 4
 #endif
 constexpr int kMaxPagesPerWave = LASER_ATTN_MAX_PPS;
-constexpr int kLongestRun = 128;       // pages per wave, where longer runs save a round of workgroups
-constexpr int kWidePagesPerWave = 16;  // the same for prefill forwards of more than kMaxRows rows
+constexpr int kWidePagesPerWave = 16;  // longest run of prefill forwards of more than kMaxRows rows
 // Splits of a one-row group that merges inside the attention kernel: its last workgroup reads
 // every split's partial (G columns x (hd + 2) floats each), so fewer, longer splits shorten
 // that tail; the bound trades it against how many workgroups stream the group's pages.
@@ -1117,8 +1116,8 @@ static int plan_groups(const laser_model* m, const laser_kv* kv, Plan& p, int sl
   }
   // A work item (workgroup) takes one 16-column query tile of a group and spreads a split of
   // its pages over its 4 waves.  Splits of at most kMaxPagesPerWave pages per wave, enough
-  // of them to give about kTargetAttnWaves waves; a group of several tiles lists its splits
-  // in chunks of 8, tile by tile, so that the tiles of one split are 8 items apart (workgroups
+  // of them to give about kTargetAttnWaves waves, or longer ones (run_pages; kWidePagesPerWave in
+  // wide prefills); a group of several tiles lists its splits in chunks of 8, tile by tile, so that the tiles of one split are 8 items apart (workgroups
   // go to the 8 XCDs in turn: they share one XCD's L2).  Partial slots of a row: its
   // shared-pages group's splits, then its own group's; own groups next to a shared one get at
   // most kOwnSlots splits.
@@ -1149,20 +1148,11 @@ static int plan_groups(const laser_model* m, const laser_kv* kv, Plan& p, int sl
     base = 2 * wgs >= m->cus ? kWidePagesPerWave : std::min(kWidePagesPerWave, std::max(base, (int)(units / kTargetAttnWaves)));
   }
   if (p.M <= kMaxRows) {
-    // Longer runs until every workgroup is resident at once: a workgroup keeps its pages streaming,
-    // so one round of long runs beats several rounds of short ones, each with its own start-up and
-    // partials (68k positions, batch 8, 8B: 63.5 us with runs of at most 4 pages, 52.9 with one
-    // round), and a last round that is nearly empty costs most (runs of 16 pages: 1.4 rounds, the
-    // step 840 against 800 us).
     const int pos_bytes = d.head_dim * m->kv_es;  // a wave's ring takes 64 of these, of 160 KB per CU
     const int resident = m->cus * (pos_bytes >= 512 ? 1 : pos_bytes >= 256 || tiles == 2 ? 2 : 3);
-    auto workgroups = [&](int b) {
-      long long n = 0;
-      for (int i = 0; i < p.n_groups; ++i)
-        n += (long long)ceil_div(p.groups[i].npages - p.groups[i].pbeg, kAttnWaves * b) * ntiles(p.groups[i]) * d.n_kv_heads;
-      return n;
-    };
-    while (base < kLongestRun && workgroups(base) > resident) ++base;
+    RunGroup rg[kMaxGroups];
+    for (int i = 0; i < p.n_groups; ++i) rg[i] = RunGroup{p.groups[i].npages - p.groups[i].pbeg, ntiles(p.groups[i])};
+    base = run_pages(rg, p.n_groups, d.n_kv_heads, kAttnWaves, resident, base);
   }
   auto item_count = [&]() {
     int n = 0;

@@ -79,3 +79,29 @@ def test_two_tiles_per_item(kind, hd, S):
         check_prob(conf[b].item(), res.confidence, f"{shape.name} confidence of request {b}")
     kv.destroy()
     model.destroy()
+
+
+@pytest.mark.parametrize("kind", ["bf16", "fp8"])
+@pytest.mark.parametrize("lens", [[100 + i % 5 for i in range(40)] + [14000] + [90] * 23, [1500 + i % 9 for i in range(64)]],
+                         ids=["one-long", "even"])
+def test_batches_of_64(kind, lens):
+    # one long request among many short ones (short runs), and an even batch whose every request is one
+    # workgroup per KV head (runs of 24 pages)
+    require_gpu()
+    shape = ModelShape(f"runs64-{kind}", 1, 256, 16, 8, 64, 352, 515, False, True, "bf16", 1.0e4, 1.0e-5,
+                       "fp8" if kind == "fp8" else "")
+    max_pos, B = 14336, len(lens)
+    model, orc, _ = make_pair(shape, max_rows=64, max_positions=max_pos, cache_oracle=True)
+    kv = _filled(model, shape, lens, 8, max_pos)
+    tok = synth.make_tokens(B, shape.vocab, 3200)
+    d_tok, nxt, p = tok.cuda(), torch.zeros(B, dtype=torch.int32, device="cuda"), torch.zeros(B, device="cuda")
+    lg = torch.zeros(B, shape.vocab, device="cuda")
+    L.laser_decode_step(model, kv, list(range(B)), d_tok, nxt, p, lg)
+    torch.cuda.synchronize()
+    assert torch.isfinite(lg).all()
+    for b in (0, 3, 39, 40, 41, 63):
+        ref = orc.decode_token(_state(shape, lens[b], b, max_pos), int(tok[b]))
+        compare_logits(lg[b].cpu().numpy(), ref, f"{shape.name} request {b} ({lens[b]} positions)")
+        check_prob(p[b].item(), lm_stats(ref)[1], f"{shape.name} request {b}")
+    kv.destroy()
+    model.destroy()
