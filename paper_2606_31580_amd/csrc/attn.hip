@@ -490,8 +490,9 @@ __global__ __launch_bounds__(64 * kAttnWaves) void k_attn(AttnArgs a) {
   __syncthreads();
   if (s_tk != (unsigned)(fuse_n - 1)) return;
   constexpr int CH = HD / 4;  // 4-dim chunks of a column
-  if (tid < NQ * CH) {
-    const int cc = tid / CH, d4 = tid - cc * CH;
+  // (a group size above 8 at head dim 128 is more chunks than threads)
+  for (int ch = tid; ch < NQ * CH; ch += 64 * kAttnWaves) {
+    const int cc = ch / CH, d4 = ch - cc * CH;
     const size_t colb = (size_t)wi.row0 * a.G + cc;
     float M = -INFINITY, Ls = 0.f;
     f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};

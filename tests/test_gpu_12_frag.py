@@ -155,3 +155,31 @@ def test_merge_in_attention(shape, max_rows, rows):
     assert torch.isfinite(out[1]).all()
     assert float((out[0] - out[1]).abs().max()) <= 2e-3
     model.destroy()
+
+
+@pytest.mark.parametrize("group,hd", [(8, 128), (9, 128), (16, 128), (16, 64)])
+def test_merge_in_attention_large_groups(group, hd):
+    # One-row groups of up to 16 query heads per KV head, merged inside the attention kernel: group
+    # x head dim / 4 chunks, more than its 256 threads above 8 heads of 128.  Against the merge
+    # kernel; only the order of the fp32 merge differs.
+    require_gpu()
+    shape = ModelShape("merge-g%d" % group, 1, 64 * group, 2 * group, 2, hd, 352, 515, False, False, "bf16", 1.0e4, 1.0e-5)
+    w = {k: v.cuda() for k, v in synth.make_weights(shape).items()}
+    model = L.Model(shape, w, max_rows=3, max_positions=1024, poison=True)
+    lens = [900, 350, 600]
+    tok = synth.make_tokens(3, shape.vocab, 29).cuda()
+    out = []
+    for fused in (False, True):
+        model.set_attn_merge(fused, 128)
+        kv = L.KVCache(model, 192, 3, 64, poison=True)
+        for i, n in enumerate(lens):
+            kv.add_seq(i, n)
+            kv.import_kv(i, *synth.make_prefill_kv(shape, n, 7 + i, device="cuda"))
+        lg, p = torch.zeros(3, shape.vocab, device="cuda"), torch.zeros(3, device="cuda")
+        L.laser_decode_step(model, kv, [0, 1, 2], tok, torch.zeros_like(tok), p, lg)
+        torch.cuda.synchronize()
+        out.append(lg)
+        kv.destroy()
+    assert torch.isfinite(out[1]).all()
+    assert float((out[0] - out[1]).abs().max()) <= 2e-3
+    model.destroy()
