@@ -1260,6 +1260,11 @@ static Scratch workspace_scratch(const laser_model* m, int M) {
                  rows, std::max(1, kAttnMaxWG * m->max_rows / rows), L.frag_rows ? m->wsp<char>(L.xfrag) : nullptr};
 }
 
+// Whether a forward of M rows takes the fragment path.
+static bool takes_frag(const laser_model* m, const char* xfrag, int M) {
+  return xfrag != nullptr && m->gemm_kernel == 0 && M >= kFragMinRows;
+}
+
 static laser_status launch_forward(laser_model* m, laser_kv* kv, const FwdKey& key, hipStream_t s, const Scratch& sc,
                                    const Plan* hp);
 
@@ -1298,7 +1303,7 @@ static laser_status run_forward(laser_model* m, laser_kv* kv, Plan& p, const Pla
   key.mo = merge && sc.mcnt != nullptr && p.M <= kValuMaxRows && (d.head_dim == 64 || d.head_dim == 128) &&
            (m->oproj_merge == 2 ||
             (m->oproj_merge == 1 && (size_t)d.d_model * d.n_q_heads * d.head_dim * m->es >= kMergeMinOBytes));
-  key.frag = sc.xfrag != nullptr && m->gemm_kernel == 0 && p.M >= kFragMinRows;
+  key.frag = takes_frag(m, sc.xfrag, p.M);
   key.kv_id = kv->id;
   // The merge in the O-projection's launch: every layer's counter grows by the forward's
   // merge workgroups, and the O-projection waits for the running total.  After a forward that
@@ -1757,9 +1762,11 @@ extern "C" laser_status laser_decode_step(laser_model* m, laser_kv* kv, int batc
   return st;
 }
 
-// laser_decode_step with its scratch in the static array: the same plan and kernels, launched
-// one by one (no graph is captured or instantiated), the host plan built in the model's
-// buffer, the arrival counters cleared by a kernel.  Allocates nothing.
+// laser_decode_step with its scratch in the static array: the same plan and kernels (but a separate
+// split merge at 1-2 rows), launched one by one (no graph is captured or instantiated), the host plan
+// built in the model's buffer, the arrival counters cleared by a kernel.  Allocates nothing.  Batches
+// on the fragment path take its activations and K-share partials from the workspace, like h, q and the
+// other activations: up to kFragPartRows rows of partials would not fit the array.
 extern "C" laser_status laser_decode_step_static(laser_model* m, laser_kv* kv, int batch, const int32_t* seq_ids,
                                                  const int32_t* d_tokens, int32_t* d_next, float* d_max_prob,
                                                  float* d_logits, void* stream) {
@@ -1789,9 +1796,11 @@ extern "C" laser_status laser_decode_step_static(laser_model* m, laser_kv* kv, i
     return laser_fail(LASER_ERR_UNSUPPORTED, "batch %d needs %zu bytes of scratch; the static array holds %zu", batch,
                       off, kStaticScratchBytes);
   char* base = (char*)m->static_scratch;
-  const Scratch sc{(float*)(base + o_part), (float*)(base + o_ml), (float*)(base + o_kpart), (unsigned*)(base + o_kcnt),
-                   nullptr /* the merge kernel */, nullptr, nullptr,
-                   (unsigned*)(base + o_cnt), (LmPart*)(base + o_lm), part_bytes, ml_bytes, batch, kAttnMaxWG, nullptr};
+  const Scratch ws = workspace_scratch(m, batch);
+  const Scratch sc{(float*)(base + o_part), (float*)(base + o_ml),
+                   takes_frag(m, ws.xfrag, batch) ? ws.kpart : (float*)(base + o_kpart), (unsigned*)(base + o_kcnt),
+                   nullptr /* the merge kernel */, ws.qpart, ws.sqpart,
+                   (unsigned*)(base + o_cnt), (LmPart*)(base + o_lm), part_bytes, ml_bytes, batch, kAttnMaxWG, ws.xfrag};
   std::vector<int> seqs(seq_ids, seq_ids + batch), grow(batch, 1);
   st = check_growth(m, kv, seqs, grow);
   if (st != LASER_OK) return st;

@@ -183,3 +183,30 @@ def test_merge_in_attention_large_groups(group, hd):
     assert torch.isfinite(out[1]).all()
     assert float((out[0] - out[1]).abs().max()) <= 2e-3
     model.destroy()
+
+
+@pytest.mark.parametrize("shape,batch", [(HD64, 16), (HD64, 17), (HD64, 40), (FP8, 18)],
+                         ids=lambda v: v.name if isinstance(v, ModelShape) else None)
+def test_static_step_runs_the_same_kernels(shape, batch):
+    # The allocation-free decode step on both sides of the row count where the fragment path begins:
+    # the same kernels on the same splits as laser_decode_step, so the same bits.
+    require_gpu()
+    w = {k: v.cuda() for k, v in synth.make_weights(shape).items()}
+    model = L.Model(shape, w, max_rows=batch, max_positions=512, poison=True)
+    tok = synth.make_tokens(batch, shape.vocab, 31).cuda()
+    out = []
+    for step in (L.laser_decode_step, L.laser_decode_step_static):
+        kv = L.KVCache(model, 32 * batch, batch, 32, poison=True)
+        for i in range(batch):
+            n = 30 + 23 * (i % 19)
+            kv.add_seq(i, n)
+            kv.import_kv(i, *synth.make_prefill_kv(shape, n, 5 + i, device="cuda"))
+        lg, p = torch.zeros(batch, shape.vocab, device="cuda"), torch.zeros(batch, device="cuda")
+        for _ in range(2):
+            step(model, kv, list(range(batch)), tok, torch.zeros_like(tok), p, lg)
+        torch.cuda.synchronize()
+        out.append((lg, p))
+        kv.destroy()
+    assert torch.isfinite(out[1][0]).all()
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    model.destroy()
