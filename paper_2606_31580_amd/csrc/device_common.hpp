@@ -131,15 +131,21 @@ __device__ __forceinline__ u32x4 ld_nt16(const void* p) { return __builtin_nonte
 __device__ __forceinline__ u32x2 ld_nt8(const void* p) { return __builtin_nontemporal_load((global_ptr<u32x2>)p); }
 
 // Copies 16 bytes per lane from global memory to LDS (lane i: lds + 16 i), asynchronously; the
-// wave's vector-memory counter tells when it is there (NT: non-temporal, for what is read once).  Inline asm rather than the builtin: for
-// the builtin the compiler makes every later LDS read wait for all copies in flight.
+// wave's vector-memory counter tells when it is there (NT: non-temporal, for what is read once).
+// g is 16-byte aligned.  Inline asm rather than the builtin: for the builtin the compiler makes
+// every later LDS read wait for all copies in flight.  m0 is named as clobbered, so that the
+// compiler keeps no value of its own in it from before the copy; that it is a reserved register is
+// what the suppressed warning says.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 template <bool NT>
 __device__ __forceinline__ void copy_to_lds16(const char* g, unsigned lds) {
   if (NT)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(lds), "v"(g) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(lds), "v"(g) : "memory", "m0");
   else
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(g) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(g) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 // At most N of the wave's copies still in flight, its LDS reads done.
 template <int N>
 __device__ __forceinline__ void wait_copies() {
