@@ -39,7 +39,8 @@ __device__ __forceinline__ T ld_scalar(const void* p) {
 // RING: runs of any length (see the page copies below); else every run has at most two pages
 // (batch 1, 14k positions, 7B: 9.0 us; the ring's detour through LDS costs 0.4-0.8 us there).
 // NT: 16-column query tiles per item (2: every page serves both from one load; RING only).
-template <class KT, int HD, bool RING, int NT>
+// WALK: runs of any length without the ring, for pools or a workspace that are not 16-byte aligned.
+template <class KT, int HD, bool RING, int NT, bool WALK = false>
 __global__ __launch_bounds__(64 * kAttnWaves) void k_attn(AttnArgs a) {
   constexpr int NS = HD / 32;  // QK k-steps
   constexpr int ND = HD / 16;  // PV d-tiles
@@ -401,8 +402,15 @@ __global__ __launch_bounds__(64 * kAttnWaves) void k_attn(AttnArgs a) {
       pair(pg, I0{}, I1{});
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (a wave without pages: its copies are done too)
-  } else if (p0 < p1) {
-    pair(p0, I0{}, I1{});
+  } else {
+    for (int pg = p0; pg < p1; pg += 2) {
+      if (WALK && pg > p0) {
+        load_page(__builtin_amdgcn_readfirstlane(btrow[pg]), I0{});
+        load_page(__builtin_amdgcn_readfirstlane(btrow[min(pg + 1, plast)]), I1{});
+      }
+      pair(pg, I0{}, I1{});
+      if (!WALK) break;  // (two pages at most)
+    }
   }
   wg_barrier();  // the queries' and the rings' LDS is free: merge slots
   float* s_of = (float*)smem;
@@ -652,6 +660,7 @@ static hipError_t launch_hd(const AttnArgs& a, dim3 grid, hipStream_t s) {
     if constexpr (sizeof(KT) < 4) return launch_k(k_attn<KT, HD, true, 2>, grid, block, s, a);
     return hipErrorInvalidValue;  // (fp32 pools: one tile per item)
   }
+  if (a.long_runs && !a.ring) return launch_k(k_attn<KT, HD, false, 1, true>, grid, block, s, a);
   return a.long_runs ? launch_k(k_attn<KT, HD, true, 1>, grid, block, s, a)
                      : launch_k(k_attn<KT, HD, false, 1>, grid, block, s, a);
 }

@@ -175,6 +175,7 @@ struct AttnArgs {
   float* ml;    // [hkv][max_wg][max_rows*G][2]
   int max_wg;   // partial slots per (kv head, column): kAttnMaxWG, fewer when a wide prefill's rows share the buffer
   int long_runs;  // some item's waves walk more than two pages
+  int ring;       // workspace and pools are 16-byte aligned: long runs through the LDS rings
   int tiles;      // query tiles per item (1; 2 where a group has more than 16 columns)
   char* ofrag;  // the output as fragments for the O-projection (null: fp32 rows in o)
   uint32_t part_bytes, ml_bytes;

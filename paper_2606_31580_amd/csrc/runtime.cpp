@@ -247,6 +247,8 @@ namespace {
 
 static int ceil_div(int a, int b) { return (a + b - 1) / b; }
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+// What the kernels' copies straight to LDS ask of an array.
+static bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 // Projections of up to this many rows run on the VALU path, larger ones on the matrix cores.
 // Measured at the 7B shape: at 2 rows the VALU path is faster (riding-probe latency 13.9 vs
@@ -660,7 +662,12 @@ extern "C" laser_status laser_model_finalize(laser_model* m, int max_rows, void*
         (d.qkv_bias && (!L.bq || !L.bk || !L.bv)))
       return laser_fail(LASER_ERR_STATE, "layer %d has unset tensors", i);
   }
-  Layout L = make_layout(d, max_rows);
+  // the fragment path copies activations and weights to LDS in 16-byte pieces; other alignments keep
+  // the kernels that load them into registers
+  bool aligned = aligned16(d_workspace);
+  for (const LayerW& W : m->layers)
+    for (const void* w : {W.wq, W.wk, W.wv, W.wo, W.w_gate, W.w_up, W.w_down}) aligned &= aligned16(w);
+  Layout L = make_layout(d, max_rows, aligned);
   if (bytes < L.total) {  // a workspace for forwards of max_rows rows only: prompts go in chunks of max_rows
     const Layout narrow = make_layout(d, max_rows, false);
     if (bytes >= narrow.total) L = narrow;
@@ -1014,6 +1021,11 @@ static laser_status flush_pending(laser_kv* kv, laser_model* m, hipStream_t s, P
   return LASER_OK;
 }
 
+// Whether the attention kernel copies queries and pages through its LDS rings.
+static bool attn_ring(const laser_model* m, const laser_kv* kv) {
+  return aligned16(m->ws) && aligned16(kv->kpool) && aligned16(kv->vpool);
+}
+
 // Row groups, their attention splits and the attention work items.  Rows come in runs of one
 // sequence (spans).  Runs whose sequences start with the same page are a request and its
 // forks: they share their leading full pages, so one group over those pages holds the rows
@@ -1123,7 +1135,7 @@ static int plan_groups(const laser_model* m, const laser_kv* kv, Plan& p, int sl
   // most kOwnSlots splits.
   int tiles = 1;  // query tiles per item
   auto ntiles = [&](const GroupDesc& g) { return ceil_div(g.nrows * G, 16 * tiles); };
-  if (m->kv_es < 4) {
+  if (m->kv_es < 4 && attn_ring(m, kv)) {
     // Two tiles per item where a group has several and items of two still fill the chip: each page
     // is then loaded once for both.
     bool several = false;
@@ -1521,7 +1533,7 @@ static laser_status launch_forward(laser_model* m, laser_kv* kv, const FwdKey& k
     a.frag_out = (char*)a.act;
     a.row_scale = row_scale;
     a.tsteps = K / 32;
-    a.wtile = m->tiles_on ? tile : nullptr;
+    a.wtile = m->tiles_on && aligned16(tile) ? tile : nullptr;
     a.ksplit = fs.ks;
     a.kpart = sc.kpart;
     HIP_TRY(timed(m, cls, s, [&] {
@@ -1549,6 +1561,7 @@ static laser_status launch_forward(laser_model* m, laser_kv* kv, const FwdKey& k
   aa.max_rows = sc.rows;
   aa.max_wg = sc.max_wg;
   aa.long_runs = key.long_runs;
+  aa.ring = attn_ring(m, kv);
   aa.tiles = key.attn_tiles;
   aa.ofrag = key.frag ? m->wsp<char>(L.o) : nullptr;
   aa.scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)hd));

@@ -12,7 +12,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_helpers import compare_logits, make_pair, require_gpu
+from gpu_helpers import LOGIT_TOL, compare_logits, make_pair, require_gpu
 from oracle.transformer import SeqState
 from paper_2606_31580_amd import laser as L
 from paper_2606_31580_amd import synth
@@ -210,3 +210,62 @@ def test_static_step_runs_the_same_kernels(shape, batch):
     assert torch.isfinite(out[1][0]).all()
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
     model.destroy()
+
+
+@pytest.mark.parametrize("shape,what", [(HD64, "all"), (HD128, "all"), (FP8, "all"), (HD128, "tiles"), (HD128, "pools")],
+                         ids=lambda v: getattr(v, "name", v))
+def test_arrays_at_8_byte_boundaries(shape, what, monkeypatch):
+    # Weights, workspace, weight tiles and page pools 8 bytes past a 16-byte boundary (tensors inside
+    # one packed buffer): the copies straight to LDS ask for 16, so these calls take kernels that load
+    # into registers.  A prompt, a decode step with runs of more than two pages per wave and a probe,
+    # against the same on aligned arrays, which may take other kernels (tolerance: gpu_helpers).
+    require_gpu()
+    real = torch.empty
+
+    def moved(n, dtype=torch.uint8, device="cuda"):
+        return real(n + 24, dtype=dtype, device=device)[8:8 + n]
+
+    def at8(t):
+        out = moved(t.numel() * t.element_size()).view(t.dtype).view(t.shape)
+        out.copy_(t)
+        assert out.data_ptr() % 16 == 8
+        return out
+
+    w = {k: v.cuda() for k, v in synth.make_weights(shape).items()}
+    n_seq, n, prompt = 20, 2000, 70  # (20 x 125 pages x 2 heads over 2,048 waves: 3 pages each)
+    tok = synth.make_tokens(prompt, shape.vocab, 37).cuda()
+    suffix = synth.make_suffix(8, shape.vocab).cuda()
+    out = []
+    for move in (False, True):
+        with monkeypatch.context() as mp:  # what the binding allocates
+            if move and what == "all":
+                mp.setattr(torch, "empty", moved)
+            model = L.Model(shape, {k: at8(v) for k, v in w.items()} if move and what == "all" else w, max_rows=24,
+                            max_positions=2048, poison=True, tiles=False)
+            if move and what == "tiles":
+                mp.setattr(torch, "empty", moved)
+            model.set_tiles(True)
+            mp.setattr(torch, "empty", moved if move and what in ("all", "pools") else real)
+            kv = L.KVCache(model, 128 * (n_seq + 1), n_seq + 1, 128, poison=True)
+        assert model.workspace.data_ptr() % 16 == (8 if move and what == "all" else 0)
+        assert model.tile_buf.data_ptr() % 16 == (8 if move and what != "pools" else 0)
+        assert kv.k_pool.data_ptr() % 16 == (8 if move and what != "tiles" else 0)
+        for i in range(n_seq):
+            kv.add_seq(i, n - 7 * i)
+            kv.import_kv(i, *synth.make_prefill_kv(shape, n - 7 * i, 11 + i, device="cuda"))
+        kv.add_seq(n_seq, 0)
+        lp = torch.zeros(shape.vocab, device="cuda")
+        L.laser_prefill(model, kv, n_seq, tok, lp)
+        lg, p = torch.zeros(n_seq, shape.vocab, device="cuda"), torch.zeros(n_seq, device="cuda")
+        nxt = torch.zeros(n_seq, dtype=torch.int32, device="cuda")
+        L.laser_decode_step(model, kv, list(range(n_seq)), tok, nxt, p, lg)
+        conf, arg = torch.zeros(3, device="cuda"), torch.zeros(12, dtype=torch.int32, device="cuda")
+        lq = torch.zeros(12, shape.vocab, device="cuda")
+        L.laser_probe_confidence(model, kv, [0, 1, 2], suffix, 4, conf, arg, lq)
+        torch.cuda.synchronize()
+        out.append((lp, lg, lq.view(3, 4, -1)[:, 0]))
+        kv.destroy()
+        model.destroy()
+    for a, b in zip(*out):
+        assert torch.isfinite(b).all()
+        assert float((a - b).abs().max()) <= LOGIT_TOL
