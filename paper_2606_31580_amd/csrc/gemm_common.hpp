@@ -15,12 +15,6 @@ __device__ __forceinline__ const void* pick3(bool c0, bool c1, const void* p0, c
   return (const void*)(u0 * f0 + u1 * f1 + u2 * f2);
 }
 
-template <class T>
-__device__ __forceinline__ T* pick2(bool c0, T* p0, T* p1) {
-  const uint64_t u0 = (uint64_t)p0, u1 = (uint64_t)p1;
-  return (T*)(u0 * (uint64_t)c0 + u1 * (uint64_t)(!c0));
-}
-
 // Rotary pair gp of the QKV rows: pair (i, i + hd/2) of head h, heads numbered q, then k,
 // then v.  A workgroup holds RW/2 consecutive pairs (they may span two heads).
 struct QkvPair {

@@ -163,20 +163,19 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_frag(GemmArgs a) {
         Y[(wn * NGW + r) * YN + (16 * (wm * MTW + mt) + q4 + i) * 16 + n16] = acc[r][mt][i] * sc[mt][i];
   __syncthreads();
   const int rows = min(16 * MT, M - 16 * t0), ng = min(NG, a.n_groups - g0);
-  if (EPI == EPI_SWIGLU) {  // 8 consecutive outputs of a row: one 16-byte chunk of hi, one of lo
-    const int fst = a.F >> 5;
-    for (int idx = tid; idx < ng * rows; idx += 64 * W) {
-      const int r = idx / rows, m = idx - r * rows;
-      const float* y = Y + r * YN + m * 16;
-      float v[8];
+  // 8 consecutive outputs of a row: one 16-byte chunk of hi, one of lo
+  const int fst = a.F >> 5;
+  for (int idx = tid; idx < ng * rows; idx += 64 * W) {
+    const int r = idx / rows, m = idx - r * rows;
+    const float* y = Y + r * YN + m * 16;
+    float v[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = y[e] / (1.f + expf(-y[e])) * y[8 + e];
-      const size_t d = frag_off(16 * t0 + m, 8 * (g0 + r), fst);
-      u32x4 hi, lo;
-      split8(v, hi, lo);
-      *(u32x4*)(a.frag_out + d) = hi;
-      *(u32x4*)(a.frag_out + (d ^ 64)) = lo;
-    }
+    for (int e = 0; e < 8; ++e) v[e] = y[e] / (1.f + expf(-y[e])) * y[8 + e];
+    const size_t d = frag_off(16 * t0 + m, 8 * (g0 + r), fst);
+    u32x4 hi, lo;
+    split8(v, hi, lo);
+    *(u32x4*)(a.frag_out + d) = hi;
+    *(u32x4*)(a.frag_out + (d ^ 64)) = lo;
   }
 }
 

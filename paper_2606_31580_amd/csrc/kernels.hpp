@@ -245,10 +245,9 @@ hipError_t launch_qkv_slices(const GemmArgs& a, float* qpart, float* sqpart, hip
 #define LASER_FRAG_SHAPES                                                                                     \
   LASER_FRAG(2, 1, 1, 4, 6) LASER_FRAG(2, 1, 1, 5, 6) LASER_FRAG(2, 1, 1, 7, 6) LASER_FRAG(2, 1, 1, 8, 6)     \
   LASER_FRAG(2, 1, 1, 10, 6) LASER_FRAG(3, 1, 1, 4, 6) LASER_FRAG(3, 1, 1, 5, 6) LASER_FRAG(3, 1, 1, 7, 6)    \
-  LASER_FRAG(3, 1, 1, 8, 6) LASER_FRAG(3, 1, 1, 10, 6) LASER_FRAG(4, 1, 1, 4, 6) LASER_FRAG(4, 1, 1, 5, 6)    \
-  LASER_FRAG(4, 1, 1, 7, 6) LASER_FRAG(4, 1, 1, 8, 6) LASER_FRAG(4, 1, 1, 10, 6) LASER_FRAG(4, 2, 2, 2, 3)    \
-  LASER_FRAG(3, 4, 2, 2, 3) LASER_FRAG(4, 3, 2, 2, 3) LASER_FRAG(4, 4, 2, 2, 3) LASER_FRAG(4, 5, 2, 2, 3)     \
-  LASER_FRAG(4, 4, 4, 2, 3) LASER_FRAG(4, 5, 4, 2, 3)
+  LASER_FRAG(3, 1, 1, 8, 6) LASER_FRAG(3, 1, 1, 10, 6) LASER_FRAG(4, 1, 1, 5, 6) LASER_FRAG(4, 1, 1, 7, 6)    \
+  LASER_FRAG(4, 1, 1, 8, 6) LASER_FRAG(4, 1, 1, 10, 6) LASER_FRAG(3, 4, 2, 2, 3) LASER_FRAG(4, 3, 2, 2, 3)    \
+  LASER_FRAG(4, 4, 2, 2, 3) LASER_FRAG(4, 5, 2, 2, 3) LASER_FRAG(4, 4, 4, 2, 3) LASER_FRAG(4, 5, 4, 2, 3)
 constexpr int frag_cfg(int mtw, int ngw, int wm, int wn) { return mtw * 1000 + ngw * 100 + wm * 20 + wn; }
 constexpr int kFragPartRows = 2048;
 hipError_t launch_gemm_frag(int epi, int cfg, const GemmArgs& a, hipStream_t s);
