@@ -267,13 +267,16 @@ laser_status laser_model_set_tensor(laser_model* m, const char* name, const void
 
 /* Bytes of device workspace the model needs for forwards of up to max_rows rows
  * (tokens per forward: batch for decode, S*batch for a probe chunk; 1..64).  For bf16 models
- * with d_ffn a multiple of 32 it includes room for prompts prefilled 512 tokens at a time. */
+ * with d_ffn a multiple of 32 it includes room for prompts prefilled 512 tokens at a time (about
+ * 100 MB at the 7B shape), whatever max_rows is. */
 laser_status laser_workspace_size(const laser_model* m, int max_rows, size_t* bytes);
 
-/* Checks that every tensor is set, lays out the caller's workspace (>= the size above
- * for max_rows; without the room for wide prefills, prompts run max_rows tokens at a time) and fills its constant tables (RoPE cos/sin computed on the host in
- * double precision) with asynchronous copies on `stream`.  The workspace must stay
- * allocated until laser_model_destroy. */
+/* Checks that every tensor is set, lays out the caller's workspace and fills its constant
+ * tables (RoPE cos/sin computed on the host in double precision) with asynchronous copies on
+ * `stream`.  The workspace must stay allocated until laser_model_destroy.  It has the size above
+ * for max_rows, or a smaller one without the room for wide prefills (the INVALID_ARG message of
+ * a call with fewer bytes names both): prompts then run max_rows tokens at a time, and so they do
+ * with weights or a workspace that are not 16-byte aligned. */
 laser_status laser_model_finalize(laser_model* m, int max_rows, void* d_workspace, size_t bytes, void* stream);
 laser_status laser_model_destroy(laser_model* m);
 

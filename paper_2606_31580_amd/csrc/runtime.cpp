@@ -495,7 +495,7 @@ static Layout make_layout(const laser_model_desc& d, int max_rows, bool wide = t
   L.kcnt = take(L.kcnt_bytes);  // their arrival counters (zero between kernels)
   L.mcnt_bytes = (size_t)d.n_layers * kMgReplicas * kKsCntStride * 4;
   L.mcnt = take(L.mcnt_bytes);  // merge counters of the O-projection's launch (replicas per layer)
-  if (qkv_slices_fit(d, max_rows)) {  // K-slice partials of the QKV projection of wide forwards
+  if (!L.frag_rows && qkv_slices_fit(d, max_rows)) {  // K-slice partials of QKV, where fragments don't take it
     const size_t nsl = ceil_div(d.d_model, kQSliceSteps * 32);
     L.qpart = take(nsl * max_rows * (size_t)(d.n_q_heads + 2 * d.n_kv_heads) * hd * 4);
     L.sqpart = take(nsl * max_rows * 4);
@@ -668,11 +668,11 @@ extern "C" laser_status laser_model_finalize(laser_model* m, int max_rows, void*
   for (const LayerW& W : m->layers)
     for (const void* w : {W.wq, W.wk, W.wv, W.wo, W.w_gate, W.w_up, W.w_down}) aligned &= aligned16(w);
   Layout L = make_layout(d, max_rows, aligned);
-  if (bytes < L.total) {  // a workspace for forwards of max_rows rows only: prompts go in chunks of max_rows
-    const Layout narrow = make_layout(d, max_rows, false);
-    if (bytes >= narrow.total) L = narrow;
-  }
-  if (!d_workspace || bytes < L.total) return laser_fail(LASER_ERR_INVALID_ARG, "workspace of %zu bytes needed", L.total);
+  const Layout narrow = make_layout(d, max_rows, false);  // forwards of max_rows rows only: prompts in chunks of max_rows
+  if (bytes < L.total && bytes >= narrow.total) L = narrow;
+  if (!d_workspace || bytes < L.total)
+    return laser_fail(LASER_ERR_INVALID_ARG, "workspace of %zu bytes needed (%zu without prompts in wide forwards)", L.total,
+                      narrow.total);
   if (L.attn_part_bytes >= (1ull << 31))  // read by buffer instructions with 32-bit offsets
     return laser_fail(LASER_ERR_UNSUPPORTED, "attention partials of %zu bytes exceed 2 GiB", L.attn_part_bytes);
   hipStream_t s = (hipStream_t)stream;

@@ -8,6 +8,8 @@ two forwards), appended to an empty or a non-empty context, with callers' row li
 same library with the K-split kernel (laser_model_set_gemm_kernel mode 1), which runs it in
 chunks of the caller's rows: appended K/V within one rounding step of their storage type.
 Tolerances are the parity protocol's (gpu_helpers)."""
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -264,6 +266,54 @@ def test_arrays_at_8_byte_boundaries(shape, what, monkeypatch):
         L.laser_probe_confidence(model, kv, [0, 1, 2], suffix, 4, conf, arg, lq)
         torch.cuda.synchronize()
         out.append((lp, lg, lq.view(3, 4, -1)[:, 0]))
+        kv.destroy()
+        model.destroy()
+    for a, b in zip(*out):
+        assert torch.isfinite(b).all()
+        assert float((a - b).abs().max()) <= LOGIT_TOL
+
+
+@pytest.mark.parametrize("shape,max_rows", [(HD64, 1), (HD128, 16), (HD128, 40), (FP8, 64)], ids=lambda v: getattr(v, "name", v))
+def test_workspace_without_wide_prefills(shape, max_rows, monkeypatch):
+    # The smaller workspace that finalize takes: prompts in chunks of max_rows, no fragments, and
+    # nothing written past its end.  Against the same calls with the full workspace, whose projections
+    # sum in another order (tolerance: gpu_helpers).
+    require_gpu()
+    w = {k: v.cuda() for k, v in synth.make_weights(shape).items()}
+    prompt = synth.make_tokens(97, shape.vocab, 43).cuda()
+    tok = synth.make_tokens(max_rows, shape.vocab, 47).cuda()
+    real, sizes, out = L._call, [], []
+
+    def call(name, *a):
+        if name != "laser_model_finalize":
+            return real(name, *a)
+        with pytest.raises(L.LaserError) as e:
+            real(name, *a[:3], 16, *a[4:])
+        full, small = (int(x) for x in re.findall(r"\d+", str(e.value).split("workspace of")[1])[:2])
+        assert full == a[3] and small < full
+        sizes.append(small)
+        with pytest.raises(L.LaserError):
+            real(name, *a[:3], small - 1, *a[4:])
+        return real(name, *a[:3], small, *a[4:])
+
+    for small in (False, True):
+        with monkeypatch.context() as mp:
+            if small:
+                mp.setattr(L, "_call", call)
+            model = L.Model(shape, w, max_rows=max_rows, max_positions=512, poison=True)
+        kv = L.KVCache(model, 32 * (max_rows + 1), max_rows + 1, 32, poison=True)
+        kv.add_seq(max_rows, 0)
+        lp = torch.zeros(shape.vocab, device="cuda")
+        L.laser_prefill(model, kv, max_rows, prompt, lp)
+        for i in range(max_rows):
+            kv.add_seq(i, 20 + 5 * i)
+            kv.import_kv(i, *synth.make_prefill_kv(shape, 20 + 5 * i, 13 + i, device="cuda"))
+        lg, p = torch.zeros(max_rows, shape.vocab, device="cuda"), torch.zeros(max_rows, device="cuda")
+        L.laser_decode_step(model, kv, list(range(max_rows)), tok, torch.zeros_like(tok), p, lg)
+        torch.cuda.synchronize()
+        out.append((lp, lg))
+        if small:
+            assert bool((model.workspace[sizes[0]:] == 0xFF).all()), "written past the workspace's end"
         kv.destroy()
         model.destroy()
     for a, b in zip(*out):
