@@ -81,7 +81,23 @@ def test_alike_groups_past_one_round(run_pages):
     assert run_pages([(188, 1)] * 24, 32) == 47
     assert run_pages([(126, 1)] * 63 + [(127, 1)], 32) == 32
     assert run_pages([(8 + 6 * i, 1) for i in range(40)], 32) == 8
-    assert run_pages([(600, 1)] * 64, 32) == 8  # runs past the longest
+    assert run_pages([(1100, 1)] * 64, 32) == 8  # runs past the longest
+
+
+@pytest.mark.parametrize("groups,b", [
+    ([(500, 1)] * 16, 125),                              # two items on every XCD, all alike
+    ([(188, 1)] * 24, 47),
+    ([(875, 1)] * 24, 219),
+    ([(500, 1)] * 8, 42),                                # three of each group
+    ([(500, 1)] * 5, 8),                                 # 20 items: three on half of the XCDs, two on the others
+    ([(500, 1)] * 17, 8),
+    ([(7 + 16 * i, 1) for i in range(16)], 8),           # 24 items of several lengths
+    ([(63 + 54 * i, 1) for i in range(16)], 8),
+    ([(7 + 10 * i, 1) for i in range(24)], 8),
+])
+def test_few_items_are_one_round_where_the_xcds_are_even(run_pages, groups, b):
+    # 32 KV heads, three workgroups per CU: at most 24 items per head are resident
+    assert run_pages(groups, 32, 768) == b
 
 
 def test_base_is_kept_where_it_fits(run_pages):

@@ -105,3 +105,31 @@ def test_batches_of_64(kind, lens):
         check_prob(p[b].item(), lm_stats(ref)[1], f"{shape.name} request {b}")
     kv.destroy()
     model.destroy()
+
+
+@pytest.mark.parametrize("lens", [[14000] * 24, [6000 - i for i in range(16)]], ids=["longest-runs", "two-per-xcd"])
+def test_few_items_per_head(lens):
+    # 32 KV heads, every request one workgroup per head: runs of 219 pages a wave, and of 94
+    require_gpu()
+    shape = ModelShape("runs-mha", 1, 256, 32, 32, 64, 352, 515, False, False, "bf16", 1.0e4, 1.0e-5)
+    max_pos, B = 14336, len(lens)
+    model, orc, _ = make_pair(shape, max_rows=64, max_positions=max_pos, cache_oracle=True)
+    kv = L.KVCache(model, sum((n + 24) // 16 + 1 for n in lens), B, max_pos // 16, poison=True)
+    k, v = synth.make_prefill_kv(shape, max(lens), 0)
+    for i, n in enumerate(lens):
+        kv.add_seq(i, n)
+        kv.import_kv(i, k[:, :n].contiguous().cuda(), v[:, :n].contiguous().cuda())
+    tok = synth.make_tokens(B, shape.vocab, 3300)
+    d_tok, nxt, p = tok.cuda(), torch.zeros(B, dtype=torch.int32, device="cuda"), torch.zeros(B, device="cuda")
+    lg = torch.zeros(B, shape.vocab, device="cuda")
+    L.laser_decode_step(model, kv, list(range(B)), d_tok, nxt, p, lg)
+    torch.cuda.synchronize()
+    assert torch.isfinite(lg).all()
+    for b in (0, B - 1):
+        n = lens[b]
+        st = SeqState.from_prefill(shape, synth.to_numpy(k[:, :n].contiguous()), synth.to_numpy(v[:, :n].contiguous()), max_pos)
+        ref = orc.decode_token(st, int(tok[b]))
+        compare_logits(lg[b].cpu().numpy(), ref, f"{shape.name} request {b} ({n} positions)")
+        check_prob(p[b].item(), lm_stats(ref)[1], f"{shape.name} request {b}")
+    kv.destroy()
+    model.destroy()
