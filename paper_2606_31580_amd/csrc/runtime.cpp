@@ -438,11 +438,10 @@ static FragShape frag_shape(int epi, int n_groups, int M, int K, int cus) {
 }
 
 // QKV over K slices (launch_qkv_slices): forwards of kQSliceMinRows to 64 rows, bf16 weights that the
-// fragment path does not take
-// (tile order when the copy is there).  Each workgroup stages a 512-column slice of K of every
-// activation row in LDS and runs 16 row groups over it.  Measured against the K-split kernel,
-// which reads all of K of every activation row for each of its one or two row groups: QKV of
-// the 8B shape at 56 rows 39.3 us against 19.5 + 6.0 us (slices, then their sum and the
+// fragment path does not take (tile order when the copy is there).  Each workgroup stages a 512-column
+// slice of K of every activation row in LDS and runs 16 row groups over it.  Measured against the
+// K-split kernel, which reads all of K of every activation row for each of its one or two row groups:
+// QKV of the 8B shape at 56 rows 39.3 us against 19.5 + 6.0 us (slices, then their sum and the
 // epilogue), at 40 rows 34.0 against 17.1 + 6.0; the 7B shape at 40 rows 30.8 against 14.4 + 6.7.
 // Other slice shapes (256 columns; 12 groups per workgroup over 6 waves) measured slower.
 constexpr int kQSliceMinRows = 33;
@@ -458,9 +457,13 @@ static size_t ks_cnt_bytes(const laser_model_desc& d) {
 
 // The fragment path (launch_gemm_frag): bf16 weights, K of every projection a multiple of 32.
 // Forwards of kFragMinRows rows and more take it; a prompt's prefill takes up to kFragRows rows
-// per forward, so that 256 rows read the weights once and not 4 or 16 times.  Below 17 rows (one
-// 16-row tile) the activations are a small part of what a workgroup reads and the K-split kernel
-// is at least as fast.
+// per forward, so that 256 rows read the weights once and not 4 or 16 times.  From the second 16-row
+// tile on fragments are faster, the norm and epilogue launches that they add included (decode steps
+// of requests of 300 positions, 4 layers, K-split kernel against fragments: 17 rows 396 and 349 us
+// at 1.5B, 825 and 678 at 7B, 754 and 655 at 8B; 24 rows 430 and 367, 879 and 708, 804 and 692; 32
+// rows 465 and 381, 945 and 745, 865 and 725; a prompt of 17 tokens 331 and 281, 736 and 591, 675 and
+// 576).  One tile keeps the K-split kernel, which 8 rows at 8B measured as fast with those launches
+// (the steps between are not measured on fragments: 16 rows take 351, 768 and 725 us).
 constexpr int kFragMinRows = 17;
 static bool frag_fit(const laser_model_desc& d) {
   return d.dtype == LASER_DTYPE_BF16 && d.d_ffn % 32 == 0 && d.d_model <= 16384;
@@ -1126,13 +1129,13 @@ static int plan_groups(const laser_model* m, const laser_kv* kv, Plan& p, int sl
       for (int r0 = runs[k].r0; r0 < runs[k].r1; r0 += kMaxRows)
         add_group(runs[k].seq, r0, std::min(r0 + kMaxRows, runs[k].r1), f.shared, false);
   }
-  // A work item (workgroup) takes one 16-column query tile of a group and spreads a split of
-  // its pages over its 4 waves.  Splits of at most kMaxPagesPerWave pages per wave, enough
-  // of them to give about kTargetAttnWaves waves, or longer ones (run_pages; kWidePagesPerWave in
-  // wide prefills); a group of several tiles lists its splits in chunks of 8, tile by tile, so that the tiles of one split are 8 items apart (workgroups
-  // go to the 8 XCDs in turn: they share one XCD's L2).  Partial slots of a row: its
-  // shared-pages group's splits, then its own group's; own groups next to a shared one get at
-  // most kOwnSlots splits.
+  // A work item (workgroup) takes one 16-column query tile of a group (or a pair of them) and
+  // spreads a split of its pages over its 4 waves.  Splits of at most kMaxPagesPerWave pages per
+  // wave, enough of them to give about kTargetAttnWaves waves, or longer ones (run_pages;
+  // kWidePagesPerWave in wide prefills); a group of several tiles lists its splits in chunks of 8,
+  // tile by tile, so that the tiles of one split are 8 items apart (workgroups go to the 8 XCDs in
+  // turn: they share one XCD's L2).  Partial slots of a row: its shared-pages group's splits, then
+  // its own group's; own groups next to a shared one get at most kOwnSlots splits.
   int tiles = 1;  // query tiles per item
   auto ntiles = [&](const GroupDesc& g) { return ceil_div(g.nrows * G, 16 * tiles); };
   if (m->kv_es < 4 && attn_ring(m, kv)) {
@@ -1446,14 +1449,14 @@ static laser_status launch_forward(laser_model* m, laser_kv* kv, const FwdKey& k
     const FetchEmbedArgs fe = fetch_embed_args(m, kv, key, sc, hp);
     HIP_TRY(timed(m, LASER_K_EMBED, s, [&] { return launch_fetch_embed(dt, fe, key.M, s); }));
   } else {
-  HIP_TRY(timed(m, LASER_K_EMBED, s, [&] {
-    const hipError_t e = launch_plan_fetch(hp, m->wsp<Plan>(L.plans), s);
-    return e == hipSuccess ? launch_embed(dt, dp, key.M, m->embed, d.d_model, d.vocab, h, kv->bt, max_pps, s) : e;
-  }));
-  if (key.frag)
-    HIP_TRY(timed(m, LASER_K_OTHER, s, [&] {
-      return launch_resid_norm(h, nullptr, 0, key.M, d.d_model, m->layers[0].attn_norm, d.rms_eps, sc.xfrag, row_scale, s);
+    HIP_TRY(timed(m, LASER_K_EMBED, s, [&] {
+      const hipError_t e = launch_plan_fetch(hp, m->wsp<Plan>(L.plans), s);
+      return e == hipSuccess ? launch_embed(dt, dp, key.M, m->embed, d.d_model, d.vocab, h, kv->bt, max_pps, s) : e;
     }));
+    if (key.frag)
+      HIP_TRY(timed(m, LASER_K_OTHER, s, [&] {
+        return launch_resid_norm(h, nullptr, 0, key.M, d.d_model, m->layers[0].attn_norm, d.rms_eps, sc.xfrag, row_scale, s);
+      }));
   }
 
   GemmArgs base{};
