@@ -354,9 +354,10 @@ laser_status laser_decode_step(laser_model* m, laser_kv* kv, int batch, const in
  * memory (code under HIP graph capture, tight serving loops, harnesses that forbid it).
  * Same arguments, results and validation as laser_decode_step; the decode step's scratch
  * (attention split partials and statistics, the split-merge arrival counters, LM-head softmax
- * statistics, K-share partials of up to 16 rows) lives in a static device array of 32 MiB per
- * GPU, held from the library's first use on that GPU until the process ends, instead of in the
- * model's workspace.  The kernels are launched one by one (no graph is captured or instantiated), the
+ * statistics, K-share partials) lives in a static device array of 32 MiB per GPU, held from
+ * the library's first use on that GPU until the process ends, instead of in the model's
+ * workspace (but for the K-share partials of batches of 17 rows and more whose projections run
+ * on fragments: those stay in the workspace).  The kernels are launched one by one (no graph is captured or instantiated), the
  * host plan is built in a buffer the model allocated at finalize, and the arrival counters
  * are cleared by a kernel at every call (the array keeps the previous call's contents).
  * Calls that overlap on one GPU (any model, any stream) race on the array: order them.
